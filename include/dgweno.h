@@ -212,7 +212,10 @@ int dg_step_static(const dg_mesh_desc* desc, double* U, double dt, double t);
  * step, the stabilisation of Secs. 3 and 4 re-evaluated in every stage.
  * The stage launches (3, 2 or 6 per step; one fused launch per step where
  * dg_set_fused selects it) are recorded once into a HIP graph (cached for the
- * same U, dt and chunk length) and replayed on the context stream.  With
+ * same U, dt and chunk length) and replayed on the context stream.  In 1D a
+ * run of two or more steps takes many steps per launch instead, without a
+ * graph (the steps of a whole mesh of up to 256 cells, a window of cells and
+ * its halo beyond; bitwise the same results), unless dg_set_fused is 0.  With
  * bc_kind RIEMANN the stages read their times (on which the exterior state
  * depends) as offsets from a device copy of the context clock, which a
  * one-thread launch sets before each replay, so the same graph serves any
@@ -267,7 +270,8 @@ int dg_get_tile(const dg_ctx* ctx, int32_t* tx, int32_t* ty);
  * tiles exceed LDS (2D degree 4), rk_order is not 3 or bc_kind is not
  * CONSTANT; in those cases the automatic mode never uses it.  dg_get_fused
  * writes 1 if steps use it.
- * Mode 0 also makes the adjoint (below) launch its two passes of every stage
+ * Mode 0 also makes dg_run of a 1D problem launch its stages one by one, and
+ * the adjoint (below) launch its two passes of every stage
  * separately instead of sharing launches between consecutive stages; the
  * result is bitwise the same either way. */
 int dg_set_fused(dg_ctx* ctx, int32_t mode);

@@ -261,22 +261,14 @@ int rk2_step(dg_ctx* c, hipStream_t st, double* U, double dt, double t) {
   return stage(c, st, c->U1, U, U, nullptr, 0.5, 0.5, dt, 0, t + dt);
 }
 
-// Shu-Osher coefficients of the five-stage fourth-order SSP method (Spiteri
-// and Ruuth): U_k = sum_j alpha_kj U_j + beta_kj dt L(U_j).
-constexpr double kA10 = 1.0, kB10 = 0.391752226571890;
-constexpr double kA20 = 0.444370493651235, kA21 = 0.555629506348765, kB21 = 0.368410593050371;
-constexpr double kA30 = 0.620101851488403, kA32 = 0.379898148511597, kB32 = 0.251891774271694;
-constexpr double kA40 = 0.178079954393132, kA43 = 0.821920045606868, kB43 = 0.544974750228521;
-constexpr double kA52 = 0.517231671970585, kA53 = 0.096059710526147, kB53 = 0.063692468666290;
-constexpr double kA54 = 0.386708617503269, kB54 = 0.226007483236906;
-
-// The five-stage step in place, as stage launches of the form
+// The five-stage fourth-order step in place, as stage launches of the form
 // out = a un + b (uin + dt' L(uin)) with dt' = dt beta / alpha.  The last
 // stage needs L(U3) and L(U4); L(U3) is evaluated twice (for U4 and for the
 // partial sum W = a52 U2 + a53 U3 + b53 dt L(U3)) so that every launch
 // remains one stage kernel.  Buffers: U1 <- U1, U3; U2 <- U2, W; U3 <- U4.
 // The stage states' times follow from the same combination applied to t' = 1.
 int rk54_step(dg_ctx* c, hipStream_t st, double* U, double dt, double t0) {
+  using namespace dgk;  // its coefficients
   int rc;
   double *A = c->U1, *B = c->U2, *C = c->U3;
   const double t1 = kA10 * t0 + kB10 * dt;
@@ -296,6 +288,53 @@ int ssp_step(dg_ctx* c, hipStream_t st, double* U, double dt, double t) {
   if (c->d.rk_order == 2) return rk2_step(c, st, U, dt, t);
   if (c->d.rk_order == 4) return rk54_step(c, st, U, dt, t);
   return rk3_step_to(c, st, U, U, dt, nullptr, nullptr, t);
+}
+
+// Whether runs take the 1D kernel of many steps per launch (line_kernel): any
+// order, except where the fused step kernels are switched off.
+bool uses_line(const dg_ctx* c) { return c->d.dim == 1 && c->fused_mode != 0; }
+
+// nsteps >= 2 steps of a 1D problem on U in place.  A mesh of one workgroup
+// is updated in place; otherwise the launches alternate between U and U1
+// (windows read their neighbours' cells), an even number of them.
+int line_steps(dg_ctx* c, hipStream_t st, double* U, double dt, int nsteps) {
+  using namespace dgk;
+  LaunchReq r{};
+  r.kind = LAUNCH_LINE;
+  r.flux = c->d.flux;
+  r.mode = c->d.mode;
+  r.order = c->d.rk_order;
+  r.stream = st;
+  r.line.s = base_args(c);
+  double* d = r.line.dts;
+  d[0] = d[1] = d[2] = dt;
+  if (r.order == 4) {
+    d[0] = dt * kB10 / kA10;
+    d[1] = dt * kB21 / kA21;
+    d[2] = dt * kB32 / kA32;
+    d[3] = dt * kB43 / kA43;
+    d[4] = dt * kB53 / kA53;
+    d[5] = dt * kB54 / kA54;
+  }
+  const bool one = c->d.nx <= kLineThreads;
+  const LinePlan p = line_plan(c->d.nx, c->nl, r.order, c->cus, one ? kLineChunk : (nsteps + 1) / 2);
+  r.threads = p.threads;
+  r.line.own = p.own;
+  int launches = (nsteps + p.steps - 1) / p.steps;
+  if (!one) launches += launches & 1;
+  double* cur = U;
+  double* other = one ? U : c->U1;
+  for (int k = 0; k < launches; ++k) {
+    // the steps spread evenly over the launches
+    r.line.steps = (int)((long long)nsteps * (k + 1) / launches - (long long)nsteps * k / launches);
+    r.line.halo = one ? 0 : rk_evals(r.order) * r.line.steps;
+    r.line.s.uin = cur;
+    r.line.s.out = other;
+    const hipError_t e = c->launch(&r);
+    if (e != hipSuccess) return hip_fail(e, "line kernel launch");
+    std::swap(cur, other);
+  }
+  return DG_OK;
 }
 
 // len SSP steps on U in place.  With the fused kernel (three-stage method
@@ -1027,6 +1066,12 @@ int dg_run(dg_ctx* c, double* U, double dt, int32_t nsteps) {
 
 // dg_run's steps (arguments checked by the caller)
 static int run_steps(dg_ctx* c, double* U, double dt, int32_t nsteps) {
+  // 1D: many steps per launch, so there is nothing for a graph to save
+  if (uses_line(c) && nsteps >= 2) {
+    const int rc = line_steps(c, c->stream, U, dt, nsteps);
+    if (rc == DG_OK) c->t += nsteps * dt;
+    return rc;
+  }
   // whole chunks of up to 64 steps replay one captured graph; a remainder
   // replays a second graph of its own length (both cached per (U, dt, length)).
   // Under BC_RIEMANN the stages read their times from the device clock,

@@ -2,12 +2,13 @@
 #pragma once
 
 #include "dg_adjoint.hpp"
+#include "dg_line.hpp"
 
 namespace dgk {
 
 enum LaunchKind { LAUNCH_STAGE = 0, LAUNCH_PROJECT = 1, LAUNCH_LAMBDA = 2, LAUNCH_BATCH = 3,
                   LAUNCH_ADJ_SENSOR = 4, LAUNCH_ADJ_GRAD = 5, LAUNCH_STEP = 6, LAUNCH_ADJ_GRAD_SENSOR = 7,
-                  LAUNCH_SIGNATURE = 8 };
+                  LAUNCH_SIGNATURE = 8, LAUNCH_LINE = 9 };
 
 // the fused step kernel's tiles: 256 cells in 1D; in 2D 16 columns of
 // kStepTile2D or kStepTile2DHalf rows (LAUNCH_STEP: args.ty)
@@ -33,6 +34,8 @@ struct LaunchReq {
   BatchStageArgs batch;  // LAUNCH_BATCH (tile shape in args.tx/args.ty, grid in ncells)
   int batch_one;         // LAUNCH_BATCH: one workgroup per tile (grid = batch.ntiles)
   AdjArgs adj;           // LAUNCH_ADJ_* (tile shape in adj.s.tx/adj.s.ty)
+  LineArgs line;         // LAUNCH_LINE (1D; line.s, not args)
+  int order, threads;    // LAUNCH_LINE: Runge-Kutta order, threads per workgroup
   uint32_t* sig;         // LAUNCH_SIGNATURE: branch records [3][cells] (stage input in args.uin)
 };
 

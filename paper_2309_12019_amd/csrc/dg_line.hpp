@@ -1,0 +1,235 @@
+// Device code: many SSP Runge-Kutta steps of a 1D problem in one launch (the
+// scalar fluxes and the Euler system, the second-, third- and fourth-order
+// methods).
+//
+// One thread holds one cell in registers from the first step of the launch to
+// the last; a stage publishes the cells' states in LDS, passes one barrier
+// and evaluates every cell from its registers and its two neighbours' slots
+// (two LDS buffers in turn, so one barrier per operator evaluation is
+// enough).  A mesh of at most kLineThreads cells is one workgroup, periodic
+// wrap and walls included, and its steps run without leaving it.  A larger
+// mesh is cut into windows of kLineThreads cells: a window loads `halo` cells
+// on each side of the `own` cells it stores, and every operator evaluation
+// makes one more cell at each end of it stale, so halo = evaluations per step
+// x steps.  Stale cells are computed like the others and never stored.  The
+// cell arithmetic and the RK combinations are those of the per-stage kernels
+// in the same order: the results are the same bit for bit.
+//
+// What bounds it: a small mesh is one chain of dependent FP64 operations, LDS
+// round trips and barriers per evaluation on a few waves, and a launch per
+// step (or per stage) spends more time between the launches than in them; a
+// large one is bound by its arithmetic, where the threads of a launch per
+// step idle at the tile's ends (five waves for 262 of 320 cells) and the
+// per-stage Euler kernel moves the state seven times a step.  Per step, one
+// launch per step or stage -> this kernel: 64 cells P2 advection 4.4 -> 2.0
+// us, 1024 cells P3 fourth order 17.4 -> 4.3, Sod 128 cells P2 8.0 -> 5.5,
+// Sod 2^20 cells P2 121 -> 79.
+#pragma once
+
+#include "dg_euler.hpp"
+
+namespace dgk {
+
+constexpr int kLineThreads = 256;
+
+// Coefficients of the SSP methods in the form out = a un + b (u + dt' L(u)).
+// The five-stage fourth-order method of Spiteri and Ruuth (Shu-Osher form
+// U_k = sum_j alpha_kj U_j + beta_kj dt L(U_j)); dt' = dt beta / alpha.
+constexpr double kA10 = 1.0, kB10 = 0.391752226571890;
+constexpr double kA20 = 0.444370493651235, kA21 = 0.555629506348765, kB21 = 0.368410593050371;
+constexpr double kA30 = 0.620101851488403, kA32 = 0.379898148511597, kB32 = 0.251891774271694;
+constexpr double kA40 = 0.178079954393132, kA43 = 0.821920045606868, kB43 = 0.544974750228521;
+constexpr double kA52 = 0.517231671970585, kA53 = 0.096059710526147, kB53 = 0.063692468666290;
+constexpr double kA54 = 0.386708617503269, kB54 = 0.226007483236906;
+
+// operator evaluations of one step of the method of this order (the
+// fourth-order method uses L(U3) in two combinations)
+__host__ __device__ constexpr int rk_evals(int order) { return order == 4 ? 5 : order; }
+
+struct LineArgs {
+  StageArgs s;   // uin, out (the same array only for a mesh of one workgroup), mesh and parameters
+  int steps;     // steps of this launch
+  int own;       // cells a workgroup stores (the whole mesh: nx)
+  int halo;      // cells it loads on each side of them (the whole mesh: 0)
+  double dts[6]; // dt' of the combinations, in order (fourth order: U1 U2 U3 U4 W U^{n+1})
+};
+
+// Thread t of the workgroup of window `tile`: its cell's mesh index before
+// wrapping (gx), whether it holds a cell of the window (else it only joins
+// the barriers), and whether it stores it.  own + 2 halo <= the workgroup's
+// threads.
+__host__ __device__ inline bool line_cell(const LineArgs& B, int tile, int t, int& gx, bool& stores) {
+  gx = tile * B.own - B.halo + t;
+  stores = t >= B.halo && t < B.halo + B.own && gx < B.s.nx;
+  return t < B.own + 2 * B.halo;
+}
+
+// Launch shape for a mesh of nx cells and (at most) `steps` steps per launch.
+// Up to kLineThreads cells: one workgroup, any number of steps.  Beyond:
+// windows of kLineThreads threads, and as many steps per launch as pay.  A
+// longer launch hides more of a launch's fixed time (kLineFixed: the gap to
+// the next launch, the loads and the stores) and recomputes more halo cells.
+// While every window has a compute unit of its own the halo costs nothing, so
+// the longest launch wins (halo <= 48 of 256 threads); past that the sum of
+// the two costs is minimised, with kLineEval us of a compute unit's time per
+// operator evaluation of a window and stored value of a cell.
+constexpr int kLineMaxHalo = 48;
+constexpr int kLineChunk = 128;  // steps per launch of a mesh of one workgroup
+constexpr double kLineFixed = 4.0, kLineEval = 0.14;
+struct LinePlan {
+  int threads, own, halo, steps;
+};
+inline LinePlan line_plan(int nx, int nv, int order, int cus, int steps) {
+  if (nx <= kLineThreads) return {(nx + 63) / 64 * 64, nx, 0, steps};
+  const int ev = rk_evals(order);
+  LinePlan best{};
+  double cost = 0.0;
+  for (int s = 1; s <= kLineMaxHalo / ev && s <= steps; ++s) {
+    const int own = kLineThreads - 2 * ev * s;
+    const double load = (double)((nx + own - 1) / own) / cus;
+    const double c = ev * kLineEval * nv * (load > 1.0 ? load : 1.0) + kLineFixed / s;
+    if (s == 1 || c < cost) {
+      cost = c;
+      best = {kLineThreads, own, ev * s, s};
+    }
+  }
+  return best;
+}
+
+// dU/dt of one cell of a scalar flux, from its coefficients and the slots of
+// its neighbours
+template <int P, int FLUX, int MODE>
+struct LineCell {
+  using G = TileGeom<1, kLineThreads, 1>;
+  using C = Cell<1, P, FLUX, MODE, G::S, G::W>;
+  static constexpr int NV = P + 1, S = G::S;
+  __device__ static inline void rhs(const StageArgs& A, const double* b, const double (&c)[NV], int ix,
+                                    double (&L)[NV]) {
+    double gam;
+    C::template rhs<true>(A, b, c, ix, 0, L, gam);
+  }
+};
+
+template <int P, int MODE>
+struct LineCell<P, FLUX_EULER, MODE> {
+  using E = EulerCell<P, MODE, kLineThreads>;
+  using C = typename E::C;
+  static constexpr int N = P + 1, NV = 3 * N, S = E::S;
+  __device__ static inline void rhs(const StageArgs& A, const double* b, const double (&c)[NV], int ix,
+                                    double (&L)[NV]) {
+    double u[3][N], R[3][N], lam;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) u[j / N][j % N] = c[j];
+    const double gam = C::template gamma_of<true>(A, b, u[0], ix, 0);
+    E::residual(A, b, u, ix, R, lam);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      double Lk[N];
+      C::finish(A, u[k], gam, lam, R[k], Lk);
+#pragma unroll
+      for (int a = 0; a < N; ++a) L[k * N + a] = Lk[a];
+    }
+  }
+};
+
+__host__ __device__ constexpr int line_lds_doubles(int nv) { return 2 * nv * TileGeom<1, kLineThreads, 1>::S; }
+
+// Grid: ceil(nx / own) workgroups of at most kLineThreads threads (a multiple
+// of 64), LDS line_lds_doubles.
+template <int P, int FLUX, int MODE, int RK>
+__global__ void __launch_bounds__(kLineThreads) line_kernel(const LineArgs B) {
+  using LC = LineCell<P, FLUX, MODE>;
+  constexpr int NV = LC::NV, S = LC::S;
+  extern __shared__ double lds[];
+  const StageArgs& A = B.s;
+  const int t = threadIdx.x;
+  int gx, wx = 0, wy;
+  bool stores;
+  const bool held = line_cell(B, xcd_tile(blockIdx.x, gridDim.x), t, gx, stores);
+  // cells beyond a non-periodic end hold the exterior state in every stage
+  const bool active = held && step_cell<1>(A, gx, 0, wx, wy);
+  double c[NV], u0[NV];
+#pragma unroll
+  for (int j = 0; j < NV; ++j) c[j] = active ? A.uin[(size_t)wx * NV + j] : (j == 0 ? A.bc : 0.0);
+  // cell t at slot t + 1; on a periodic mesh of one workgroup each end cell
+  // also fills the slot beyond the other end
+  const bool ring = B.halo == 0 && A.per_x;
+  // otherwise the slots beyond the workgroup's cells hold the exterior state
+  // (only stale cells and the ends of a non-periodic mesh read them)
+  if (t < 2 && !ring) {
+    const int end = t == 0 ? 0 : (B.own + 2 * B.halo) + 1;
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int j = 0; j < NV; ++j) lds[(k * NV + j) * S + end] = j == 0 ? A.bc : 0.0;
+  }
+  int par = 0;
+  // L := L(c); the state is published in this evaluation's buffer first
+  auto eval = [&](double (&L)[NV]) {
+    double* const buf = lds + par * (NV * S);
+    par ^= 1;
+    if (held) {
+#pragma unroll
+      for (int j = 0; j < NV; ++j) buf[j * S + t + 1] = c[j];
+      if (ring && t == 0) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j) buf[j * S + B.own + 1] = c[j];
+      }
+      if (ring && t == B.own - 1) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j) buf[j * S] = c[j];
+      }
+    }
+    tile_barrier();
+    if (active) LC::rhs(A, buf + t + 1, c, wx, L);
+  };
+  // v = a un + b (c + dt L), rounded as in the per-stage kernels (contraction
+  // off: with a = 1 the compiler would fuse b (..) + un, which they do not)
+  auto comb = [&](double a, double b, double dt, const double (&L)[NV], const double (&un)[NV], double (&v)[NV]) {
+#pragma clang fp contract(off)
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const double w = b * fma(dt, L[j], c[j]);
+      v[j] = a != 0.0 ? fma(a, un[j], w) : w;
+    }
+  };
+#pragma unroll 1
+  for (int s = 0; s < B.steps; ++s) {
+    double L[NV];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) u0[j] = c[j];
+    eval(L);
+    if (active) comb(0.0, 1.0, B.dts[0], L, u0, c);
+    if constexpr (RK == 2) {
+      eval(L);
+      if (active) comb(0.5, 0.5, B.dts[1], L, u0, c);
+    } else if constexpr (RK == 3) {
+      eval(L);
+      if (active) comb(0.75, 0.25, B.dts[1], L, u0, c);
+      eval(L);
+      if (active) comb(1.0 / 3.0, 2.0 / 3.0, B.dts[2], L, u0, c);
+    } else {
+      double u2[NV], w[NV];
+      eval(L);
+      if (active) comb(kA20, kA21, B.dts[1], L, u0, c);
+#pragma unroll
+      for (int j = 0; j < NV; ++j) u2[j] = c[j];
+      eval(L);
+      if (active) comb(kA30, kA32, B.dts[2], L, u0, c);
+      eval(L);
+      if (active) {
+        comb(kA52, kA53, B.dts[4], L, u2, w);  // W = a52 U2 + a53 U3 + b53 dt L(U3)
+        comb(kA40, kA43, B.dts[3], L, u0, c);
+      }
+      eval(L);
+      if (active) comb(1.0, kA54, B.dts[5], L, w, c);
+    }
+  }
+  if (active && stores) {
+    double* const dst = A.out + (size_t)gx * NV;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) dst[j] = c[j];
+  }
+}
+
+}  // namespace dgk

@@ -288,6 +288,38 @@ hipError_t launch_euler(int mode, const StageArgs& A, hipStream_t s) {
   }
 }
 
+// many steps of a 1D problem in one launch (line_kernel)
+template <int FLUX, int MODE, int RK>
+hipError_t launch_line_fmr(const LaunchReq* r) {
+  const LineArgs& B = r->line;
+  auto k = line_kernel<DGK_P, FLUX, MODE, RK>;
+  const size_t lds = sizeof(double) * (size_t)line_lds_doubles(LineCell<DGK_P, FLUX, MODE>::NV);
+  if (lds > 65536) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k, dim3((B.s.nx + B.own - 1) / B.own), dim3(r->threads), lds, r->stream, B);
+  return hipGetLastError();
+}
+
+template <int FLUX, int MODE>
+hipError_t launch_line_fm(const LaunchReq* r) {
+  if (r->order == 2) return launch_line_fmr<FLUX, MODE, 2>(r);
+  if (r->order == 4) return launch_line_fmr<FLUX, MODE, 4>(r);
+  return launch_line_fmr<FLUX, MODE, 3>(r);
+}
+
+template <int FLUX>
+hipError_t launch_line_f(const LaunchReq* r) {
+  switch (r->mode) {
+    case MODE_DG: return launch_line_fm<FLUX, MODE_DG>(r);
+    case MODE_LO: return launch_line_fm<FLUX, MODE_LO>(r);
+    case MODE_ZHAO: return launch_line_fm<FLUX, MODE_ZHAO>(r);
+    default: return launch_line_fm<FLUX, MODE_WENO>(r);
+  }
+}
+
 // branch records of a stage input (linear and Burgers fluxes, modes DG, LO,
 // WENO: the adjoint's coverage), on the context's tile
 template <int FLUX, int MODE, int TX, int TY>
@@ -379,6 +411,14 @@ extern "C" hipError_t DGK_CAT(dgk_launch, DGK_DIM, DGK_P)(const LaunchReq* r) {
       // the adjoint covers the linear and Burgers fluxes
       if (r->flux == FLUX_LINADV) return launch_adj_f<FLUX_LINADV>(r);
       if (r->flux == FLUX_BURGERS) return launch_adj_f<FLUX_BURGERS>(r);
+      return hipErrorInvalidValue;
+    }
+    case LAUNCH_LINE: {
+      if constexpr (DGK_DIM == 1) {
+        if (r->flux == FLUX_LINADV) return launch_line_f<FLUX_LINADV>(r);
+        if (r->flux == FLUX_BURGERS) return launch_line_f<FLUX_BURGERS>(r);
+        return launch_line_f<FLUX_EULER>(r);
+      }
       return hipErrorInvalidValue;
     }
     case LAUNCH_SIGNATURE: {

@@ -1,0 +1,58 @@
+// Host-only check of line_kernel's windows: every mesh cell is stored by
+// exactly one thread, the loads and LDS slots stay inside their buffers, and
+// a stored cell is further from the window's ends than the launch has
+// operator evaluations.
+#include <cstdio>
+#include <vector>
+
+#include "../../paper_2309_12019_amd/csrc/dg_line.hpp"
+
+using namespace dgk;
+
+int main() {
+  int bad = 0, launches = 0;
+  const int slots = TileGeom<1, kLineThreads, 1>::S;
+  for (int nx : {1, 2, 63, 64, 65, 128, 255, 256, 257, 300, 511, 512, 1000, 4099, 65536, 70001, 1 << 20})
+    for (int order : {2, 3, 4})
+      for (int nv : {2, 5, 15})
+        for (int steps : {1, 2, 5, 64})
+          for (int per : {0, 1}) {
+            const LinePlan p = line_plan(nx, nv, order, 256, steps);
+            LineArgs B{};
+            B.s.nx = nx;
+            B.s.ny = 1;
+            B.s.per_x = per;
+            B.own = p.own;
+            B.halo = p.halo;
+            const bool one = nx <= kLineThreads;
+            const int ev = rk_evals(order);
+            bad += p.threads % 64 != 0 || p.threads > kLineThreads || p.own < 1 || p.steps < 1 || p.steps > steps;
+            bad += p.own + 2 * p.halo > p.threads || (one ? p.halo != 0 || p.own != nx : p.halo != ev * p.steps);
+            std::vector<int> written(nx, 0);
+            const int grid = (nx + p.own - 1) / p.own;
+            for (int tile = 0; tile < grid; ++tile)
+              for (int t = 0; t < p.threads; ++t) {
+                int gx, wx, wy;
+                bool stores;
+                const bool held = line_cell(B, tile, t, gx, stores);
+                if (!held) {
+                  bad += stores;
+                  continue;
+                }
+                bad += t + 1 >= slots - 1 || p.own + 2 * p.halo + 1 >= slots;
+                if (step_cell<1>(B.s, gx, 0, wx, wy)) {
+                  bad += wx < 0 || wx >= nx;
+                  if (stores) {
+                    bad += wx != gx;
+                    if (wx == gx) ++written[gx];
+                    // beyond the window's ends lies another window's cell, or the mesh's end
+                    if (!one) bad += t < ev * p.steps || p.own + 2 * p.halo - 1 - t < ev * p.steps;
+                  }
+                }
+              }
+            for (int e = 0; e < nx; ++e) bad += written[e] != 1;
+            ++launches;
+          }
+  std::printf("%d launches, %d failures\n", launches, bad);
+  return bad ? 1 : 0;
+}
