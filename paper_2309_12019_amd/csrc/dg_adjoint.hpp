@@ -304,7 +304,8 @@ struct AdjCell {
     for (int f = 0; f < NF; ++f) {
       C::template cand_any<0>(f, b, cd);
       beta[f + 1] = C::qform(cd);
-      al[f + 1] = has[f] ? A.wnb * C::weight(A, beta[f + 1]) : 0.0;
+      const double wl = A.wnb * C::weight(A, beta[f + 1]);
+      al[f + 1] = has[f] ? wl : 0.0;
       m += has[f];
       if constexpr (SB) __builtin_amdgcn_sched_barrier(0);
     }
@@ -635,7 +636,7 @@ struct AdjCell {
     if constexpr (MODE != MODE_DG) {
       double gam = 1.0;
       const double* zo = nullptr;
-      if constexpr (MODE == MODE_WENO) {
+      if constexpr (is_weno(MODE)) {
         zo = Ad.z + cell;
         gam = zo[Z::GA * zs];
       }
@@ -662,7 +663,7 @@ struct AdjCell {
         }
       }
       // ---- sensor records: own and the face neighbours'
-      if constexpr (MODE == MODE_WENO) {
+      if constexpr (is_weno(MODE)) {
         double d[NL], bc[NL];
 #pragma unroll
         for (int j = 0; j < NL; ++j) d[j] = zo[j * zs];

@@ -170,6 +170,9 @@ StageArgs base_args(const dg_ctx* c) {
   return A;
 }
 
+// the kernels' mode for the descriptor's mode and exponents
+int kmode(const dg_mesh_desc& d) { return dgk::kernel_mode(d.mode, d.q, d.weno_pow); }
+
 size_t stage_lds_bytes(int dim, int nl, int p, int flux, int tx, int ty) {
   return sizeof(double) * (size_t)dgk::stage_kernel_lds_doubles(dim, nl, p, flux, tx, dim == 2 ? ty : 1);
 }
@@ -189,7 +192,7 @@ int stage(dg_ctx* c, hipStream_t st, const double* uin, const double* un, double
   LaunchReq r{};
   r.kind = dgk::LAUNCH_STAGE;
   r.flux = c->d.flux;
-  r.mode = c->d.mode;
+  r.mode = kmode(c->d);
   r.args = base_args(c);
   r.args.tclock = c->tclock;
   // 8x8 tiles of several waves on meshes of a few tiles per compute unit:
@@ -239,7 +242,7 @@ int step_fused(dg_ctx* c, hipStream_t st, const double* Un, double* Uout, double
   LaunchReq r{};
   r.kind = dgk::LAUNCH_STEP;
   r.flux = c->d.flux;
-  r.mode = c->d.mode;
+  r.mode = kmode(c->d);
   r.args = base_args(c);
   r.args.uin = Un;
   r.args.un = Un;
@@ -302,7 +305,7 @@ int line_steps(dg_ctx* c, hipStream_t st, double* U, double dt, int nsteps) {
   LaunchReq r{};
   r.kind = LAUNCH_LINE;
   r.flux = c->d.flux;
-  r.mode = c->d.mode;
+  r.mode = kmode(c->d);
   r.order = c->d.rk_order;
   r.stream = st;
   r.line.s = base_args(c);
@@ -490,7 +493,7 @@ int adj_launch(dg_ctx* c, hipStream_t st, int kind, const double* U, const doubl
   LaunchReq r{};
   r.kind = kind;
   r.flux = c->d.flux;
-  r.mode = c->d.mode;
+  r.mode = kmode(c->d);
   r.stream = st;
   r.adj.s = base_args(c);
   r.adj.s.uin = U;

@@ -52,6 +52,7 @@ constexpr int kMaxBranches = 4;
 
 struct Class {
   int dim, p, flux, mode, nl;
+  int kmode;                  // the kernels' mode (MODE_WENO1 where every problem has the paper's exponents)
   std::vector<int> probs;     // problem indices
   // schedule
   int tx = 0, ty = 1, grid_per_cu = 0, order = 0, branch = 0;  // grid_per_cu 0: one workgroup per tile
@@ -125,7 +126,7 @@ int class_stage(dg_batch* b, Class& c, hipStream_t st, const double* uin, const 
   LaunchReq r{};
   r.kind = dgk::LAUNCH_BATCH;
   r.flux = c.flux;
-  r.mode = c.mode;
+  r.mode = c.kmode;
   r.args.tx = c.tx;
   r.args.ty = c.ty;
   r.ncells = class_grid(b, c);
@@ -251,6 +252,9 @@ int dg_batch_create(const dg_mesh_desc* descs, int32_t count, dg_batch** out) {
     c.p = d.p;
     c.flux = d.flux;
     c.mode = d.mode;
+    c.kmode = dgk::kernel_mode(d.mode, d.q, d.weno_pow);
+    for (int i : probs)
+      if (dgk::kernel_mode(b->d[i].mode, b->d[i].q, b->d[i].weno_pow) != c.kmode) c.kmode = d.mode;
     c.nl = nl_of(d);
     c.tx = d.dim == 1 ? 256 : 16;
     c.ty = d.dim == 1 ? 1 : 16;
@@ -446,7 +450,7 @@ int dg_batch_run_sequential(dg_batch* b, double* arena, const double* dts, int32
         LaunchReq r{};
         r.kind = dgk::LAUNCH_STAGE;
         r.flux = d.flux;
-        r.mode = d.mode;
+        r.mode = dgk::kernel_mode(d.mode, d.q, d.weno_pow);
         r.args = b->args[i];
         r.args.tx = d.dim == 1 ? 256 : 16;
         r.args.ty = d.dim == 1 ? 1 : 16;

@@ -29,6 +29,18 @@ namespace dgk {
 
 enum { FLUX_LINADV = 0, FLUX_BURGERS = 1, FLUX_KPP = 2, FLUX_EULER = 3 };  // KPP: 2D; EULER: 1D system
 enum { MODE_DG = 0, MODE_LO = 1, MODE_WENO = 2, MODE_ZHAO = 3 };
+// Kernel mode of MODE_WENO problems with the paper's exponents (q = 1,
+// weno_pow = 2): the sensor then has no branch and no call to a general
+// power.  Branches between a candidate's reads and its use let the compiler
+// sink the sums of all candidates behind the last of them, with every
+// candidate live in registers (2D stage kernels, P2 125 -> 92-104 VGPRs, P3
+// 230 -> 170, P4 312 -> 231-254: two waves per SIMD instead of one).
+enum { MODE_WENO1 = 4 };
+__host__ __device__ constexpr bool is_weno(int mode) { return mode == MODE_WENO || mode == MODE_WENO1; }
+// the kernel mode for a problem's mode and exponents
+__host__ __device__ constexpr int kernel_mode(int mode, double q, double wpow) {
+  return mode == MODE_WENO && q == 1.0 && wpow == 2.0 ? (int)MODE_WENO1 : mode;
+}
 // exterior state at non-periodic faces: the constant bc, or (2D Burgers only)
 // the exact solution of the four-quadrant problem of Sec. 5.4 at time t
 enum { BC_CONSTANT = 0, BC_RIEMANN = 1 };
@@ -206,6 +218,15 @@ __host__ __device__ inline int wrap_index(int x, int n) {
   if (x < 0) return x + n;
   while (x >= n) x -= n;
   return x;
+}
+
+// Values that are complete at this point: without it the compiler sinks the
+// arithmetic that forms them behind a later branch (to where they are used),
+// while the LDS reads it needs stay in front of the branch, all live.
+template <int N>
+__device__ inline void settle(double (&v)[N]) {
+#pragma unroll
+  for (int j = 0; j < N; ++j) asm volatile("" : "+v"(v[j]));
 }
 
 // 1/x to near full precision: hardware estimate and two Newton steps
@@ -416,7 +437,7 @@ struct Cell {
 
   __device__ static inline double weight(const StageArgs& A, double beta) {
     const double t = A.eps + beta;
-    if (A.wpow == 2.0) {
+    if (MODE == MODE_WENO1 || A.wpow == 2.0) {
       const double r = rcp(t);
       return r * r;
     }
@@ -446,7 +467,8 @@ struct Cell {
     for (int f = 0; f < NF; ++f) {
       double cd[NL];
       cand_any<0>(f, b, cd);
-      const double al = has[f] ? A.wnb * weight(A, qform(cd)) : 0.0;
+      const double wl = A.wnb * weight(A, qform(cd));  // (first, so that the choice is a select)
+      const double al = has[f] ? wl : 0.0;
       asum += al;
 #pragma unroll
       for (int j = 1; j < NL; ++j) acc[j] = fma(al, cd[j], acc[j]);
@@ -462,6 +484,12 @@ struct Cell {
 #pragma unroll
     for (int j = 1; j < NL; ++j) cs[j] = fma(-inv, acc[j], c[j]);
     const double num2 = qform(cs);
+    if constexpr (MODE == MODE_WENO1) {
+      double ratio = sqrt_pos(num2 * rcp(beta0));
+      ratio = beta0 == 0.0 ? __builtin_inf() : ratio;
+      ratio = num2 == 0.0 ? 0.0 : ratio;
+      return ratio >= A.bthr ? fmin(1.0, ratio) : 0.0;
+    }
     double ratio;
     if (num2 == 0.0)
       ratio = 0.0;
@@ -665,7 +693,8 @@ struct Cell {
     for (int f = 0; f < NF; ++f) {
       double cd[NL];
       cand_any<0>(f, b, cd);
-      al[f + 1] = has[f] ? A.wnb * weight(A, qform(cd)) : 0.0;
+      const double wl = A.wnb * weight(A, qform(cd));
+      al[f + 1] = has[f] ? wl : 0.0;
       asum += al[f + 1];
       if constexpr (SB) __builtin_amdgcn_sched_barrier(0);
     }
@@ -706,14 +735,19 @@ struct Cell {
   // for sensor(); the arithmetic is the same either way.  The three parts
   // (gamma_of, residual, finish) may also run on different threads.
   // XBC: compile the BC_RIEMANN exterior state in (the per-stage kernel only).
+  // gam_out, where given, receives gamma_e, before the residual: a branch
+  // after the arithmetic lets the compiler sink the arithmetic behind it, past
+  // the LDS reads that it needs.  (The kernels with the general sensor, whose
+  // branches do that anyway, keep the store at the end: 1 % faster there.)
   template <bool SB = true, bool XBC = false>
   __device__ static inline void rhs(const StageArgs& A, const double* b, const double (&c)[NL], int ix, int iy,
-                                    double (&L)[NL], double& gam_out) {
+                                    double (&L)[NL], double* gam_out = nullptr) {
     const double gam = gamma_of<SB>(A, b, c, ix, iy);
-    gam_out = gam;
+    if (MODE != MODE_WENO && gam_out) *gam_out = gam;
     double R[NL], lam;
     residual<XBC>(A, b, c, ix, iy, R, lam);
     finish(A, c, gam, lam, R, L);
+    if (MODE == MODE_WENO && gam_out) *gam_out = gam;
   }
 
   // The moments of face f of the cell (0: -x, 1: +x, 2: -y, 3: +y), oriented
@@ -954,7 +988,7 @@ struct Cell {
                                          uint32_t (&v)[3]) {
     auto fold = [](uint32_t h, uint32_t x) { return (h ^ x) * 16777619u; };
     v[0] = v[1] = v[2] = 2166136261u;
-    if constexpr (MODE == MODE_WENO) v[0] = fold(v[0], (gam >= 1.0 ? 1u : 0u) | (gam == 0.0 ? 2u : 0u));
+    if constexpr (is_weno(MODE)) v[0] = fold(v[0], (gam >= 1.0 ? 1u : 0u) | (gam == 0.0 ? 2u : 0u));
     if constexpr (FLUX == FLUX_BURGERS) {
       double umax = 0.0;
       uint32_t arg = 0xffffu, sgn = 0;
@@ -1301,9 +1335,11 @@ __device__ inline void stage_tile(const StageArgs& A, double* lds, int ix0, int 
     tile_barrier();
   }
   if (active) {
-    double L[NL], gam;
+    double L[NL];
+    double* const gam_out = A.gamma ? A.gamma + cell : nullptr;
     if constexpr (SHARE) {
-      gam = C::template gamma_of<true>(A, lds + sc, c, gx, gy);
+      const double gam = C::template gamma_of<true>(A, lds + sc, c, gx, gy);
+      if (gam_out) *gam_out = gam;
       double R[NL], lam;
       C::template residual<false, false>(A, lds + sc, c, gx, gy, R, lam);
       const int lx = t % TX, ly = t / TX;
@@ -1318,9 +1354,9 @@ __device__ inline void stage_tile(const StageArgs& A, double* lds, int ix0, int 
       }
       C::finish(A, c, gam, lam, R, L);
     } else {
-      C::template rhs<true, XBC>(A, lds + sc, c, gx, gy, L, gam);
+      C::template rhs<true, XBC>(A, lds + sc, c, gx, gy, L, gam_out);
     }
-    if (A.gamma) A.gamma[cell] = gam;
+    if constexpr (MODE != MODE_WENO) settle(L);
     double* dst = A.out + cell * NL;
     if (A.rhs_only) {
 #pragma unroll
@@ -1341,12 +1377,19 @@ __device__ inline void stage_tile(const StageArgs& A, double* lds, int ix0, int 
   }
 }
 
+// Waves per SIMD the stage kernels are held to: two at P4, where their
+// registers are within a few of the limit for it (231-262 of 256 VGPRs, up
+// to 15 spilled).
+__host__ __device__ constexpr int stage_min_waves(int dim, int p, int mode) {
+  return dim == 2 && p == 4 && mode == MODE_WENO1 ? 2 : 1;
+}
+
 // The fused stage kernel.  Grid: (ceil(nx/TX), ceil(ny/TY)), one tile each,
 // in the XCD-aware order of xcd_tile.  XBC: the BC_RIEMANN exterior state
 // compiled in (2D Burgers; launched for that exterior state only, since the
 // checks cost every cell ~4 % of its instructions).
 template <int DIM, int P, int FLUX, int MODE, int TX, int TY, bool XBC = false>
-__global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX) stage_kernel(const StageArgs A) {
+__global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX, stage_min_waves(DIM, P, MODE)) stage_kernel(const StageArgs A) {
   extern __shared__ double lds[];
   const int tile = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
   const int bx = tile % gridDim.x, by = tile / gridDim.x;
@@ -1467,6 +1510,7 @@ __device__ inline void roles_tile(const StageArgs& A, double* lds, int ix0, int 
   }
   double L[NL];
   C::finish(A, c, gaml[lc], lam, R, L);
+  settle(L);
   const size_t cell = (size_t)gy * nx + gx;
   if (A.gamma) A.gamma[cell] = gaml[lc];
   double* dst = A.out + cell * NL;
@@ -1598,6 +1642,7 @@ __device__ inline void kpp_split_tile(const StageArgs& A, double* lds, int ix0, 
   }
   double L[NL];
   C::finish(A, c, gam, lam, R, L);
+  settle(L);
   const size_t cell = (size_t)gy * nx + gx;
   if (A.gamma) A.gamma[cell] = gam;
   double* dst = A.out + cell * NL;
@@ -1808,7 +1853,7 @@ __device__ inline void step_stage(const StageArgs& A, const double* tin, const d
   // by the scheduling barrier do not raise the occupancy
   constexpr bool SB = DIM == 1 || P > 2;
   constexpr int NF_ = split_full(TO::N, G::NT);  // cells evaluated whole
-  constexpr bool SPLIT = (MODE == MODE_WENO || MODE == MODE_ZHAO) && NF_ < TO::N;
+  constexpr bool SPLIT = (is_weno(MODE) || MODE == MODE_ZHAO) && NF_ < TO::N;
   const int nx = A.nx, ny = DIM == 2 ? A.ny : 1;
 
   // RK combination of cell o and its store (to the output tile, or to HBM)
@@ -1846,10 +1891,10 @@ __device__ inline void step_stage(const StageArgs& A, const double* tin, const d
     for (int o = threadIdx.x; o < TO::N; o += G::NT) {
       int islot, aslot, wx, wy;
       if (!locate(o, true, islot, aslot, wx, wy)) continue;
-      double c[NL], L[NL], gam;
+      double c[NL], L[NL];
 #pragma unroll
       for (int j = 0; j < NL; ++j) c[j] = tin[j * TI::S + islot];
-      C::template rhs<SB>(A, tin + islot, c, wx, wy, L, gam);
+      C::template rhs<SB>(A, tin + islot, c, wx, wy, L);
       store(o, aslot, wx, wy, c, L);
     }
   } else {
@@ -1864,8 +1909,8 @@ __device__ inline void step_stage(const StageArgs& A, const double* tin, const d
 #pragma unroll
       for (int j = 0; j < NL; ++j) c[j] = tin[j * TI::S + islot];
       if (role == 0) {
-        double L[NL], gam;
-        C::template rhs<SB>(A, tin + islot, c, wx, wy, L, gam);
+        double L[NL];
+        C::template rhs<SB>(A, tin + islot, c, wx, wy, L);
         store(o, aslot, wx, wy, c, L);
       } else if (role == 1) {
         gx_lds[o - NF_] = C::template gamma_of<SB>(A, tin + islot, c, wx, wy);
@@ -1945,11 +1990,29 @@ struct BatchStageArgs {
   double a, b;
 };
 
+// A struct of the tables above, which no kernel writes, from an address that
+// is the same for the whole workgroup: through the constant address space,
+// so that its fields are scalar loads into SGPRs.  As ordinary loads they
+// come through the vector cache into some 80 VGPRs.
+template <class T>
+__device__ inline T load_uniform(const T* p) {
+  static_assert(sizeof(T) % 8 == 0 && alignof(T) <= 8, "copied in words of 8 bytes");
+  typedef const __attribute__((address_space(4))) uint64_t* Words;
+  const Words w = (Words)(uintptr_t)p;
+  uint64_t v[sizeof(T) / 8];
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(T) / 8; ++i) v[i] = w[i];
+  T t;
+  __builtin_memcpy(&t, v, sizeof(T));
+  return t;
+}
+
 template <int DIM, int P, int FLUX, int MODE, int TX, int TY>
 __device__ inline void batch_tile(const BatchStageArgs& B, double* lds, int k) {
-  const BatchTile tl = B.tiles[k];
-  StageArgs A = B.probs[tl.prob].args;
-  const long long off = B.probs[tl.prob].off;
+  const BatchTile tl = load_uniform(B.tiles + k);
+  const BatchProblem pr = load_uniform(B.probs + tl.prob);
+  StageArgs A = pr.args;
+  const long long off = pr.off;
   A.uin = B.uin + off;
   A.un = B.un + off;
   A.out = B.out + off;
@@ -1964,7 +2027,8 @@ __device__ inline void batch_tile(const BatchStageArgs& B, double* lds, int k) {
 // a loop makes the compiler keep the arithmetic's loop-invariant values in
 // registers across tiles (tens of VGPRs more), which this form avoids.
 template <int DIM, int P, int FLUX, int MODE, int TX, int TY, bool ONE = false>
-__global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX) batch_stage_kernel(const BatchStageArgs B) {
+__global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX, stage_min_waves(DIM, P, MODE))
+    batch_stage_kernel(const BatchStageArgs B) {
   extern __shared__ double lds[];
   if constexpr (ONE) {
     if ((int)blockIdx.x < B.ntiles) batch_tile<DIM, P, FLUX, MODE, TX, TY>(B, lds, blockIdx.x);

@@ -105,8 +105,7 @@ struct LineCell {
   static constexpr int NV = P + 1, S = G::S;
   __device__ static inline void rhs(const StageArgs& A, const double* b, const double (&c)[NV], int ix,
                                     double (&L)[NV]) {
-    double gam;
-    C::template rhs<true>(A, b, c, ix, 0, L, gam);
+    C::template rhs<true>(A, b, c, ix, 0, L);
   }
 };
 
