@@ -196,15 +196,18 @@ int stage(dg_ctx* c, hipStream_t st, const double* uin, const double* un, double
   r.args = base_args(c);
   r.args.tclock = c->tclock;
   // 8x8 tiles of several waves on meshes of a few tiles per compute unit:
-  // the KPP flux by split_waves; the others four waves up to three tiles
-  // per compute unit (per step, 192^2 P2 rotation 17.1 -> 15.7 us at 2.25
-  // tiles per CU, but 256^2 20.4 -> 23.1 at four)
+  // the KPP flux by split_waves; the others four waves (roles_kernel) up to
+  // as many tiles per compute unit as its registers let share one: per stage
+  // of the rotation, four waves against one, P1 3.40 / 3.43 us at 1 and 3.56 /
+  // 3.52 at 1.27; P2 5.44 / 5.66 at 2.4 and 6.35 / 6.56 at 4; P3 6.83 / 7.69
+  // at 1.6 and 9.58 / 8.65 at 2.1; P4 7.81 / 9.50 at 1 and 13.1 / 10.4 at
+  // 1.27 (Burgers alike)
   if (c->d.dim == 2 && c->tx == 8) {
     const long long t8 = (long long)((c->d.nx + 7) / 8) * ((c->d.ny + 7) / 8);
     if (c->d.flux == DG_FLUX_KPP)
       r.waves = dgk::split_waves(t8, c->cus, c->d.p);
     else
-      r.waves = t8 <= 3LL * c->cus ? 4 : 1;
+      r.waves = t8 <= (long long)dgk::roles_tiles_per_cu(c->d.p, c->d.bc_kind) * c->cus ? 4 : 1;
   }
   r.args.uin = uin;
   r.args.un = un;

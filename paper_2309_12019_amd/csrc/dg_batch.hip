@@ -258,7 +258,9 @@ int dg_batch_create(const dg_mesh_desc* descs, int32_t count, dg_batch** out) {
     c.nl = nl_of(d);
     c.tx = d.dim == 1 ? 256 : 16;
     c.ty = d.dim == 1 ? 1 : 16;
-    if (lds_bytes(c.dim, c.nl, c.flux, c.tx, c.ty) > (size_t)b->max_lds) c.tx = c.ty = 8;
+    // P4: one-wave tiles, as for single problems (128 mixed problems 740 -> 719
+    // us per step, 24 problems 276 -> 260, 400 problems 1027 -> 1008; P3 level)
+    if (lds_bytes(c.dim, c.nl, c.flux, c.tx, c.ty) > (size_t)b->max_lds || (c.dim == 2 && c.p == 4)) c.tx = c.ty = 8;
     c.probs = probs;
     c.cap = dgk::batch_tile_capacity(b->mesh, probs);
     b->cls.push_back(c);

@@ -1398,8 +1398,8 @@ __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX, stage_min_waves(DIM, 
 }
 
 // Small meshes on 8 x 8 tiles (the linear and Burgers fluxes): four waves
-// per tile.  With few tiles per compute unit (the library takes this kernel
-// up to three), one-wave tiles leave SIMDs idle and every lane runs its
+// per tile.  With few tiles per compute unit (roles_tiles_per_cu), one-wave
+// tiles leave SIMDs idle and every lane runs its
 // cell's whole stage as one dependent chain; here the parts of the stage
 // run side by side on the tile's four waves:
 //   * wave 0 loads the tile (as stage_tile does) and evaluates the volume
@@ -1413,6 +1413,13 @@ __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX, stage_min_waves(DIM, 
 // same order as stage_tile, so the same result bit for bit.
 // XBC: the BC_RIEMANN exterior state compiled in (2D Burgers).
 constexpr int kRoleThreads = 256;
+// 8 x 8 tiles per compute unit up to which this kernel is taken: what its
+// registers (four waves; 64, 123, 228 and 352 VGPRs) let run side by side; at
+// P1 one, since there its second barrier costs more than the split gains; P2
+// with the exact exterior state (twice the instructions) three
+__host__ __device__ constexpr int roles_tiles_per_cu(int p, int bc_kind) {
+  return p == 2 ? (bc_kind == BC_RIEMANN ? 3 : 4) : p == 3 ? 2 : 1;
+}
 __host__ __device__ inline int roles_lds_doubles(int nl, int n) {
   return tile_lds_doubles(2, nl, 8, 8) + face_lds_doubles(n, 8, 8) + 64;
 }
