@@ -186,8 +186,8 @@ int dg_rhs(dg_ctx* ctx, const double* U, double* dUdt, double* gamma);
  * Spiteri and Ruuth (Sec. 5.1 uses order p + 1 for its convergence study; the
  * paper does not name the fourth-order scheme).  gamma_e and lambda_e are
  * re-evaluated in every stage (Sec. 3, the stabilisation is part of the
- * semi-discrete operator).  The five-stage method evaluates the operator six
- * times per step (its last stage needs L(U^(3)) a second time).  dt must be
+ * semi-discrete operator).  The five-stage method's last stage needs L(U^(3))
+ * a second time: evaluated again in 1D stage launches, kept in 2D.  dt must be
  * finite and > 0.  With check_finite, DG_ENONFINITE if U holds NaN or Inf
  * after the step. */
 int dg_step(dg_ctx* ctx, double* U, double dt);

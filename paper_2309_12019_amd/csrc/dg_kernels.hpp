@@ -65,6 +65,11 @@ struct StageArgs {
   int tx, ty;                    // tile (one of the compiled shapes; ty = 1 in 1D)
   const double* tclock;          // BC_RIEMANN: if set, uin's time is *tclock + t (t an offset)
   double g2h;                    // 2 / h, formed on the host (the same correctly rounded quotient)
+  // a second combination of the same L, where out2 is set (2D stage kernels):
+  // out2 = a2 un2 + b2 (U^(k-1) + dt2 L); un2 and out2 may be one array
+  const double* un2;
+  double* out2;
+  double a2, b2, dt2;
   double lfac[25];               // (2/h) minv_a minv_b per coefficient a + (p+1) b (1D: (2/h) minv_a),
                                  // formed on the host in the same order (stage_lfac)
 };
@@ -1246,6 +1251,17 @@ __device__ inline void load_slot(const StageArgs& A, double* lds, int slot, int 
   for (int j = 0; j < NL; ++j) lds[j * S + slot] = v[j];
 }
 
+// The second combination of a cell's L, where the launch has one (A.out2)
+template <int NL>
+__device__ inline void store_second(const StageArgs& A, size_t cell, const double (&c)[NL], const double (&L)[NL]) {
+  if (!A.out2) return;
+  double un[NL];
+#pragma unroll
+  for (int j = 0; j < NL; ++j) un[j] = A.un2[cell * NL + j];
+#pragma unroll
+  for (int j = 0; j < NL; ++j) A.out2[cell * NL + j] = fma(A.a2, un[j], A.b2 * fma(A.dt2, L[j], c[j]));
+}
+
 // One tile of the fused stage: TX*TY threads, one per cell.  Each thread
 // loads its own cell's coefficients into registers (a wave covers a
 // contiguous span of the cell-major state) and publishes them in the
@@ -1257,7 +1273,8 @@ __device__ inline void load_slot(const StageArgs& A, double* lds, int slot, int 
 // barrier); the cells then add their faces' moments in the order of the
 // per-cell evaluation, so the result is the same bit for bit.
 // XBC: compile the BC_RIEMANN exterior state in (2D Burgers per-stage kernel).
-template <int DIM, int P, int FLUX, int MODE, int TX, int TY, bool XBC = false>
+// SECOND: compile the second combination in.
+template <int DIM, int P, int FLUX, int MODE, int TX, int TY, bool XBC = false, bool SECOND = false>
 __device__ inline void stage_tile(const StageArgs& A, double* lds, int ix0, int iy0) {
   using G = TileGeom<DIM, TX, TY>;
   using C = Cell<DIM, P, FLUX, MODE, G::S, G::W>;
@@ -1373,6 +1390,7 @@ __device__ inline void stage_tile(const StageArgs& A, double* lds, int ix0, int 
         if (comb) v = fma(A.a, un[j], v);
         dst[j] = v;
       }
+      if constexpr (SECOND) store_second(A, cell, c, L);
     }
   }
 }
@@ -1387,14 +1405,16 @@ __host__ __device__ constexpr int stage_min_waves(int dim, int p, int mode) {
 // The fused stage kernel.  Grid: (ceil(nx/TX), ceil(ny/TY)), one tile each,
 // in the XCD-aware order of xcd_tile.  XBC: the BC_RIEMANN exterior state
 // compiled in (2D Burgers; launched for that exterior state only, since the
-// checks cost every cell ~4 % of its instructions).
-template <int DIM, int P, int FLUX, int MODE, int TX, int TY, bool XBC = false>
+// checks cost every cell ~4 % of its instructions).  SECOND: the second
+// combination compiled in (launched where there is one: its code costs P2
+// kernels up to 20 VGPRs).
+template <int DIM, int P, int FLUX, int MODE, int TX, int TY, bool XBC = false, bool SECOND = false>
 __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX, stage_min_waves(DIM, P, MODE)) stage_kernel(const StageArgs A) {
   extern __shared__ double lds[];
   const int tile = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
   const int bx = tile % gridDim.x, by = tile / gridDim.x;
-  stage_tile<DIM, P, FLUX, MODE, TX, TY, XBC && DIM == 2 && FLUX == FLUX_BURGERS>(A, lds, bx * TX,
-                                                                                DIM == 2 ? by * TY : 0);
+  stage_tile<DIM, P, FLUX, MODE, TX, TY, XBC && DIM == 2 && FLUX == FLUX_BURGERS, SECOND>(A, lds, bx * TX,
+                                                                                        DIM == 2 ? by * TY : 0);
 }
 
 // Small meshes on 8 x 8 tiles (the linear and Burgers fluxes): four waves
@@ -1428,7 +1448,7 @@ __host__ __device__ inline void roles_face_task(int i, int& axis, int& e) {
   axis = i >= 72;
   e = axis ? i - 72 : i;
 }
-template <int P, int FLUX, int MODE, bool XBC>
+template <int P, int FLUX, int MODE, bool XBC, bool SECOND>
 __device__ inline void roles_tile(const StageArgs& A, double* lds, int ix0, int iy0) {
   constexpr int TX = 8, TY = 8;
   using G = TileGeom<2, TX, TY>;
@@ -1537,16 +1557,17 @@ __device__ inline void roles_tile(const StageArgs& A, double* lds, int ix0, int 
       if (comb) v = fma(A.a, un[j], v);
       dst[j] = v;
     }
+    if constexpr (SECOND) store_second(A, cell, c, L);
   }
 }
 
 // Grid as for stage_kernel on 8 x 8 tiles, kRoleThreads threads.
-template <int P, int FLUX, int MODE, bool XBC>
+template <int P, int FLUX, int MODE, bool XBC, bool SECOND = false>
 __global__ void __launch_bounds__(kRoleThreads) roles_kernel(const StageArgs A) {
   extern __shared__ double lds[];
   const int tile = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
   const int bx = tile % gridDim.x, by = tile / gridDim.x;
-  roles_tile<P, FLUX, MODE, XBC && FLUX == FLUX_BURGERS>(A, lds, bx * 8, by * 8);
+  roles_tile<P, FLUX, MODE, XBC && FLUX == FLUX_BURGERS, SECOND>(A, lds, bx * 8, by * 8);
 }
 
 // The per-stage KPP kernel on 8 x 8 tiles.  The sine and cosine at every
@@ -1569,7 +1590,7 @@ __global__ void __launch_bounds__(kRoleThreads) roles_kernel(const StageArgs A) 
 // tasks hold few registers, so they take the sine and cosine inline
 // (sincos_inl: no call frame in scratch memory; 7.8 -> 6.3 us per stage at
 // 128^2 P2, 17.1 -> 13.1 at 256^2).
-template <int P, int MODE, int V0, int NTH>
+template <int P, int MODE, int V0, int NTH, bool SECOND>
 __device__ inline void kpp_split_tile(const StageArgs& A, double* lds, int ix0, int iy0) {
   constexpr int TX = 8, TY = 8;
   using G = TileGeom<2, TX, TY>;
@@ -1649,7 +1670,8 @@ __device__ inline void kpp_split_tile(const StageArgs& A, double* lds, int ix0, 
   }
   double L[NL];
   C::finish(A, c, gam, lam, R, L);
-  settle(L);
+  // (P2 on 16 waves has registers to spare and is 1.4 % faster without)
+  if constexpr (P > 2 || NTH <= 256) settle(L);
   const size_t cell = (size_t)gy * nx + gx;
   if (A.gamma) A.gamma[cell] = gam;
   double* dst = A.out + cell * NL;
@@ -1669,6 +1691,7 @@ __device__ inline void kpp_split_tile(const StageArgs& A, double* lds, int ix0, 
       if (comb) v = fma(A.a, un[j], v);
       dst[j] = v;
     }
+    if constexpr (SECOND) store_second(A, cell, c, L);
   }
 }
 
@@ -1694,12 +1717,12 @@ __host__ __device__ constexpr int split_waves(long long tiles, int cus, int p) {
 }
 
 // Grid as for stage_kernel on 8 x 8 tiles, NTH threads.
-template <int P, int MODE, int NTH>
+template <int P, int MODE, int NTH, bool SECOND = false>
 __global__ void __launch_bounds__(NTH) kpp_split_kernel(const StageArgs A) {
   extern __shared__ double lds[];
   const int tile = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
   const int bx = tile % gridDim.x, by = tile / gridDim.x;
-  kpp_split_tile<P, MODE, split_v0(P, NTH), NTH>(A, lds, bx * 8, by * 8);
+  kpp_split_tile<P, MODE, split_v0(P, NTH), NTH, SECOND>(A, lds, bx * 8, by * 8);
 }
 
 // Branch records of the stage input (Cell::branches) of every cell, folded
@@ -2024,6 +2047,7 @@ __device__ inline void batch_tile(const BatchStageArgs& B, double* lds, int k) {
   A.un = B.un + off;
   A.out = B.out + off;
   A.gamma = nullptr;
+  A.out2 = nullptr;
   A.a = B.a;
   A.b = B.b;
   A.rhs_only = 0;

@@ -24,11 +24,14 @@ constexpr int mode16() {
   return MODE == MODE_WENO1 && (DGK_P == 1 || (DGK_P == 2 && FLUX == FLUX_LINADV)) ? (int)MODE_WENO : MODE;
 }
 
-template <int FLUX, int MODE0, int TX, int TY, bool XBC = false>
+template <int FLUX, int MODE0, int TX, int TY, bool XBC = false, bool SECOND = false>
 hipError_t launch_tile(const StageArgs& A, hipStream_t st) {
   constexpr int NL = DGK_DIM == 1 ? DGK_P + 1 : (DGK_P + 1) * (DGK_P + 1);
   constexpr int MODE = DGK_DIM == 2 && TX == 16 ? mode16<FLUX, MODE0>() : MODE0;
-  auto k = stage_kernel<DGK_DIM, DGK_P, FLUX, MODE, TX, TY, XBC>;
+  if constexpr (DGK_DIM == 2 && !SECOND) {
+    if (A.out2) return launch_tile<FLUX, MODE0, TX, TY, XBC, true>(A, st);
+  }
+  auto k = stage_kernel<DGK_DIM, DGK_P, FLUX, MODE, TX, TY, XBC, SECOND>;
   const size_t lds = sizeof(double) * (size_t)stage_lds_doubles(DGK_DIM, NL, FLUX, TX, TY);
   if (lds > 65536) {
     // tiles above 64 KB of LDS: raise the per-kernel limit to what this launch needs
@@ -43,10 +46,13 @@ hipError_t launch_tile(const StageArgs& A, hipStream_t st) {
 }
 
 // the KPP flux on 8x8 tiles: NTH / 64 waves per tile (kpp_split_kernel)
-template <int MODE, int NTH>
+template <int MODE, int NTH, bool SECOND = false>
 hipError_t launch_kpp_split_n(const StageArgs& A, hipStream_t st) {
+  if constexpr (!SECOND) {
+    if (A.out2) return launch_kpp_split_n<MODE, NTH, true>(A, st);
+  }
   constexpr int NL = (DGK_P + 1) * (DGK_P + 1);
-  auto k = kpp_split_kernel<DGK_P, MODE, NTH>;
+  auto k = kpp_split_kernel<DGK_P, MODE, NTH, SECOND>;
   const size_t lds = sizeof(double) * (size_t)split_lds_doubles(NL, quad_points(2, DGK_P, FLUX_KPP));
   if (lds > 65536) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
@@ -71,10 +77,13 @@ hipError_t launch_kpp_split(const StageArgs& A, hipStream_t st, int waves) {
 }
 
 // linear and Burgers fluxes on 8x8 tiles, four waves per tile (roles_kernel)
-template <int FLUX, int MODE, bool XBC>
+template <int FLUX, int MODE, bool XBC, bool SECOND = false>
 hipError_t launch_roles(const StageArgs& A, hipStream_t st) {
+  if constexpr (!SECOND) {
+    if (A.out2) return launch_roles<FLUX, MODE, XBC, true>(A, st);
+  }
   constexpr int NL = (DGK_P + 1) * (DGK_P + 1);
-  auto k = roles_kernel<DGK_P, FLUX, MODE, XBC>;
+  auto k = roles_kernel<DGK_P, FLUX, MODE, XBC, SECOND>;
   const size_t lds = sizeof(double) * (size_t)roles_lds_doubles(NL, DGK_P + 1);
   dim3 grid((A.nx + 7) / 8, (A.ny + 7) / 8);
   hipLaunchKernelGGL(k, grid, dim3(kRoleThreads), lds, st, A);
