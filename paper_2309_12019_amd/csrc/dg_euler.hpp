@@ -20,14 +20,38 @@ namespace dgk {
 
 constexpr double kEulerGamma = 1.4;
 
-// F(u) and |v| + c of one state
+// n / d from r = rcp(d): the quotient and one correction by its exact
+// residual, as the division instruction sequence does, without that sequence's
+// scaling of the operands (which only denormal and near-overflow values need);
+// r serves every quotient with the same denominator
+__device__ inline double div_by(double n, double d, double r) {
+  const double q = n * r;
+  return fma(fma(-d, q, n), r, q);
+}
+
+// sqrt(x): hardware estimate and two corrections by the exact residual (after
+// the first up to 1.5 units in the last place are left, after the second the
+// rounding); 0 and infinity pass through (their correction is 0 * inf),
+// negative x gives NaN
+__device__ inline double sqrt_corr(double x) {
+  const double s = __builtin_amdgcn_sqrt(x), h = 0.5 * rcp(s);
+  const double s1 = fma(h, fma(-s, s, x), s);
+  const double y = fma(h, fma(-s1, s1, x), s1);
+  return s == 0.0 || s == __builtin_inf() ? s : y;
+}
+
+// F(u) and |v| + c of one state.  Eight of these per cell and operator
+// evaluation are most of the Euler kernels' arithmetic: two divisions by the
+// density share its reciprocal, and neither they nor the square root scale
+// their operands (DIVSQRT instructions per state instead of DIVSQRT0)
 __device__ inline void euler_flux(const double (&u)[3], double (&F)[3], double& speed) {
-  const double v = u[1] / u[0];
+  const double r = rcp(u[0]);
+  const double v = div_by(u[1], u[0], r);
   const double p = (kEulerGamma - 1.0) * (u[2] - 0.5 * u[1] * v);
   F[0] = u[1];
   F[1] = fma(u[1], v, p);
   F[2] = (u[2] + p) * v;
-  speed = fabs(v) + sqrt(kEulerGamma * p / u[0]);
+  speed = fabs(v) + sqrt_corr(div_by(kEulerGamma * p, u[0], r));
 }
 
 // H . n of the LLF flux for the outward normal n = side
