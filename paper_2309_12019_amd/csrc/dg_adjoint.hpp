@@ -64,9 +64,13 @@ struct AdjCell {
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       double t = 0.0;
+      bool any = false;  // (here and below: a sum starts with its first product, not with a cleared accumulator)
 #pragma unroll
       for (int j = 1; j < NL; ++j)
-        if (TB::sn.B[i][j] != 0.0) t = fma(TB::sn.B[i][j], v[j], t);
+        if (TB::sn.B[i][j] != 0.0) {
+          t = any ? fma(TB::sn.B[i][j], v[j], t) : TB::sn.B[i][j] * v[j];
+          any = true;
+        }
       o[i] = t;
     }
   }
@@ -75,8 +79,8 @@ struct AdjCell {
   template <int F>
   __device__ static inline void cand_regs(const double (&cn)[NL], double (&cd)[NL]) {
     constexpr int si = F & 1;
-#pragma unroll
-    for (int j = 0; j < NL; ++j) cd[j] = 0.0;
+    cd[0] = 0.0;  // the constant coefficient is not used
+    // (coefficient c of a row starts with the term c == a: T[s][c][c] = 1)
     if constexpr (DIM == 1 || F < 2) {
       constexpr int R = DIM == 1 ? 1 : N;
 #pragma unroll
@@ -86,7 +90,8 @@ struct AdjCell {
 #pragma unroll
           for (int c = 0; c <= a; ++c)
             if (TB::dg.T[si][a][c] != 0.0 && (c + N * e) != 0)
-              cd[c + N * e] = fma(TB::dg.T[si][a][c], cn[a + N * e], cd[c + N * e]);
+              cd[c + N * e] = c == a ? TB::dg.T[si][a][c] * cn[a + N * e]
+                                     : fma(TB::dg.T[si][a][c], cn[a + N * e], cd[c + N * e]);
     } else {
 #pragma unroll
       for (int e = 0; e < N; ++e)
@@ -95,7 +100,8 @@ struct AdjCell {
 #pragma unroll
           for (int c = 0; c <= e; ++c)
             if (TB::dg.T[si][e][c] != 0.0 && (a + N * c) != 0)
-              cd[a + N * c] = fma(TB::dg.T[si][e][c], cn[a + N * e], cd[a + N * c]);
+              cd[a + N * c] = c == e ? TB::dg.T[si][e][c] * cn[a + N * e]
+                                     : fma(TB::dg.T[si][e][c], cn[a + N * e], cd[a + N * c]);
     }
   }
 
@@ -177,13 +183,22 @@ struct AdjCell {
 #pragma unroll
         for (int a = 0; a < N; ++a) {
           double t = 0.0;
+          bool any = false;
 #pragma unroll
           for (int a2 = 0; a2 < N; ++a2)
-            if (TB::dg.S[a][a2] != 0.0) t = fma(TB::dg.S[a][a2] * TB::dg.mhat[bb], g[a2 + N * bb], t);
+            if (TB::dg.S[a][a2] != 0.0) {
+              const double k = TB::dg.S[a][a2] * TB::dg.mhat[bb];
+              t = any ? fma(k, g[a2 + N * bb], t) : k * g[a2 + N * bb];
+              any = true;
+            }
 #pragma unroll
           for (int b2 = 0; b2 < N; ++b2)
-            if (TB::dg.S[bb][b2] != 0.0) t = fma(TB::dg.S[bb][b2] * TB::dg.mhat[a], g[a + N * b2], t);
-          o[a + N * bb] = fma(-s, t, o[a + N * bb]);
+            if (TB::dg.S[bb][b2] != 0.0) {
+              const double k = TB::dg.S[bb][b2] * TB::dg.mhat[a];
+              t = any ? fma(k, g[a + N * b2], t) : k * g[a + N * b2];
+              any = true;
+            }
+          if (any) o[a + N * bb] = fma(-s, t, o[a + N * bb]);
         }
     }
   }
@@ -343,7 +358,7 @@ struct AdjCell {
     double gam = 0.0;
     if (ratio >= A.bthr) {
       const double r1 = fmin(1.0, ratio);
-      gam = A.q == 1.0 ? r1 : pow_cold(r1, A.q);
+      gam = MODE == MODE_WENO1 || A.q == 1.0 ? r1 : pow_cold(r1, A.q);
     }
     // seed: gamma_bar = -(lambda/p) g . Khat c
     double g[NL];
@@ -358,7 +373,7 @@ struct AdjCell {
     // reverse
     double rbar = 0.0;
     if (num2 > 0.0 && den2 > 0.0 && ratio >= A.bthr && ratio <= 1.0)
-      rbar = A.q == 1.0 ? gbar : gbar * A.q * pow_cold(ratio, A.q - 1.0);
+      rbar = MODE == MODE_WENO1 || A.q == 1.0 ? gbar : gbar * A.q * pow_cold(ratio, A.q - 1.0);
     double num2b = 0.0, den2b = 0.0;
     if (rbar != 0.0) {
       const double id = rcp(den2);
@@ -372,17 +387,17 @@ struct AdjCell {
     // omega_bar_l = -dbar . cand_l
     double omb[NF + 1];
     {
-      double t = 0.0;
+      double t = db[1] * c[1];
 #pragma unroll
-      for (int j = 1; j < NL; ++j) t = fma(db[j], c[j], t);
+      for (int j = 2; j < NL; ++j) t = fma(db[j], c[j], t);
       omb[0] = -t;
     }
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
       C::template cand_any<0>(f, b, cd);
-      double t = 0.0;
+      double t = db[1] * cd[1];
 #pragma unroll
-      for (int j = 1; j < NL; ++j) t = fma(db[j], cd[j], t);
+      for (int j = 2; j < NL; ++j) t = fma(db[j], cd[j], t);
       omb[f + 1] = -t;
       if constexpr (SB) __builtin_amdgcn_sched_barrier(0);
     }
@@ -398,7 +413,7 @@ struct AdjCell {
     }
     bb[0] += den2b;
 #pragma unroll
-    for (int j = 0; j < NL; ++j) zrec[j * zs] = db[j];
+    for (int j = 1; j < NL; ++j) zrec[j * zs] = db[j];  // (dbar_0 = 0 is never read)
 #pragma unroll
     for (int l = 0; l <= NF; ++l) {
       zrec[(Z::OM + l) * zs] = om[l];
@@ -435,16 +450,19 @@ struct AdjCell {
     double tm[N], tp[N], sm[N], sp[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-      double t = 0.0, tn = 0.0, gt = 0.0, gn = 0.0;
+      double t, tn, gt, gn;
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         const int j = axis == 0 ? i + N * k : k + N * i;
-        const double so = plus ? 1.0 : TB::dg.sgn[i];
+        const double so = plus ? 1.0 : TB::dg.sgn[i];  // (sgn[0] = 1)
         const double sn = plus ? TB::dg.sgn[i] : 1.0;
-        t = fma(so, c[j], t);
-        tn = fma(sn, b[j * S + C::off(F)], tn);
-        gt = fma(so, g[j], gt);
-        gn = fma(sn * g2h * TB::dg.minv[i] * TB::dg.minv[k], bv[j * S + C::off(F)], gn);
+        const double cn = b[j * S + C::off(F)];
+        const double gf = sn * (P <= 2 ? A.lfac[i + N * k] : g2h * TB::dg.minv[i] * TB::dg.minv[k]);
+        const double vn = bv[j * S + C::off(F)];
+        t = i == 0 ? c[j] : fma(so, c[j], t);
+        tn = i == 0 ? cn : fma(sn, cn, tn);
+        gt = i == 0 ? g[j] : fma(so, g[j], gt);
+        gn = i == 0 ? gf * vn : fma(gf, vn, gn);
       }
       tm[k] = t;
       tp[k] = tn;
@@ -452,8 +470,6 @@ struct AdjCell {
       sp[k] = gn;
     }
     double acc[N];
-#pragma unroll
-    for (int k = 0; k < N; ++k) acc[k] = 0.0;
 #pragma unroll
     for (int r = 0; r < Q; ++r) {
       double um = tm[0], up = tp[0], gm = sm[0], gp = sp[0];
@@ -467,7 +483,7 @@ struct AdjCell {
       const double vax = axis == 0 ? vxl[r] : vyl[r];
       const double dl = TB::nd.w[r] * (gm - gp) * dllf(s, vax, um, up);
 #pragma unroll
-      for (int k = 0; k < N; ++k) acc[k] = fma(TB::nd.L[k][r], dl, acc[k]);
+      for (int k = 0; k < N; ++k) acc[k] = r == 0 ? TB::nd.L[k][r] * dl : fma(TB::nd.L[k][r], dl, acc[k]);
     }
 #pragma unroll
     for (int k = 0; k < N; ++k)
@@ -486,8 +502,10 @@ struct AdjCell {
     const size_t zs = (size_t)A.nx * (DIM == 2 ? A.ny : 1);  // record field stride
     double g[NL];
     scale_g(A, v, g);
+    if constexpr (DIM == 1) {
 #pragma unroll
-    for (int j = 0; j < NL; ++j) G[j] = 0.0;
+      for (int j = 0; j < NL; ++j) G[j] = 0.0;
+    }
     bool has[NF];
     has[0] = A.per_x || ix > 0;
     has[1] = A.per_x || ix < A.nx - 1;
@@ -545,7 +563,7 @@ struct AdjCell {
 #pragma unroll
           for (int a = 1; a < N; ++a) {
             t = fma(c[a + N * bb], TB::nd.L[a][qx], t);
-            tx = fma(g[a + N * bb], TB::nd.D[a][qx], tx);
+            tx = a == 1 ? g[a + N * bb] * TB::nd.D[a][qx] : fma(g[a + N * bb], TB::nd.D[a][qx], tx);
             ty = fma(g[a + N * bb], TB::nd.L[a][qx], ty);
           }
           s1[bb] = t;
@@ -554,15 +572,13 @@ struct AdjCell {
         }
         double acc[N];
 #pragma unroll
-        for (int bb = 0; bb < N; ++bb) acc[bb] = 0.0;
-#pragma unroll
         for (int qy = 0; qy < Q; ++qy) {
           double u = s1[0], gx = gx1[0], gy = 0.0;
 #pragma unroll
           for (int bb = 1; bb < N; ++bb) {
             u = fma(s1[bb], TB::nd.L[bb][qy], u);
             gx = fma(gx1[bb], TB::nd.L[bb][qy], gx);
-            gy = fma(gy1[bb], TB::nd.D[bb][qy], gy);
+            gy = bb == 1 ? gy1[bb] * TB::nd.D[bb][qy] : fma(gy1[bb], TB::nd.D[bb][qy], gy);
           }
           if (FLUX == FLUX_BURGERS && fabs(u) > vmax) {
             vmax = fabs(u);
@@ -579,15 +595,22 @@ struct AdjCell {
           }
           const double sq = TB::nd.w[qy] * fma(gx, fx, gy * fy);
 #pragma unroll
-          for (int bb = 0; bb < N; ++bb) acc[bb] = fma(TB::nd.L[bb][qy], sq, acc[bb]);
+          for (int bb = 0; bb < N; ++bb) acc[bb] = qy == 0 ? TB::nd.L[bb][qy] * sq : fma(TB::nd.L[bb][qy], sq, acc[bb]);
         }
         const double wq = TB::nd.w[qx];
 #pragma unroll
         for (int bb = 0; bb < N; ++bb)
 #pragma unroll
-          for (int a = 0; a < N; ++a) G[a + N * bb] = fma(wq * TB::nd.L[a][qx], acc[bb], G[a + N * bb]);
+          for (int a = 0; a < N; ++a) {
+            const double k = wq * TB::nd.L[a][qx];
+            G[a + N * bb] = qx == 0 ? k * acc[bb] : fma(k, acc[bb], G[a + N * bb]);
+          }
         __builtin_amdgcn_sched_barrier(0);
       }
+      // the choice of the largest |u| stays here: the branch that uses it is
+      // behind the faces, and moved there it holds every node's value
+      // (Burgers P2: 32 VGPRs)
+      if constexpr (FLUX == FLUX_BURGERS) asm volatile("" : "+v"(vmax), "+v"(vmax_u), "+v"(vmax_q));
     }
 
     // ---- faces: - sum_r w_r (g^- - g_nb^+) dH/du^- phi(r)

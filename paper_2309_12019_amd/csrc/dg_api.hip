@@ -387,11 +387,6 @@ int rk_steps(dg_ctx* c, hipStream_t st, double* U, double dt, int len, double t0
   return DG_OK;
 }
 
-int rk3_step(dg_ctx* c, hipStream_t st, double* U, double dt, double* U1 = nullptr, double* U2 = nullptr) {
-  if (!U1 && !U2) return rk_steps(c, st, U, dt, 1);
-  return rk3_step_to(c, st, U, U, dt, U1, U2);
-}
-
 int validate(const dg_mesh_desc* d) {
   if (!d) return fail(DG_EINVAL, "desc is NULL");
   if (d->dim != 1 && d->dim != 2) return fail(DG_EINVAL, "dim must be 1 or 2 (got %d)", d->dim);
@@ -501,6 +496,28 @@ int ensure_adjoint(dg_ctx* c) {
   }
   c->Z = c->Zmem;
   c->Z2 = c->Zmem + nz;
+  return DG_OK;
+}
+
+long long step_tiles16(const dg_ctx* c) {
+  return (long long)((c->d.nx + 15) / 16) * ((c->d.ny + 15) / 16);
+}
+
+// `steps` SSP-RK3 steps from `src` (only read, unless it is dst) into dst,
+// their stage states not kept: by the fused step kernel where runs take it,
+// alternating between dst and U1 so that the last step lands in dst.  At P2
+// past one 16x16 tile per compute unit, where a run's two buffers stay in the
+// caches, a sweep that stores checkpoints between steps does not (512^2
+// Burgers: 55 us per step against 53 in three stages); 400^2 P1 gains (whole
+// gradient 686 -> 627 us).
+int advance(dg_ctx* c, hipStream_t st, const double* src, double* dst, double dt, int steps) {
+  const bool fused = c->fused && (c->d.dim == 1 || c->d.p == 1 || step_tiles16(c) <= c->cus);
+  for (int k = 0; k < steps; ++k) {
+    double* out = fused && (steps - 1 - k) % 2 ? c->U1 : dst;
+    const int rc = fused && out != src ? step_fused(c, st, src, out, dt) : rk3_step_to(c, st, src, out, dt);
+    if (rc) return rc;
+    src = out;
+  }
   return DG_OK;
 }
 
@@ -770,10 +787,6 @@ bool fused_fits(const dg_ctx* c) {
   const int tx = c->d.dim == 1 ? dgk::kStepTile1D : dgk::kStepTile2D;
   const int ty = c->d.dim == 1 ? 1 : dgk::kStepTile2D;  // the larger of the two 2D tiles
   return sizeof(double) * (size_t)dgk::step_lds_doubles(c->d.dim, c->nl, tx, ty) <= (size_t)c->max_lds;
-}
-
-long long step_tiles16(const dg_ctx* c) {
-  return (long long)((c->d.nx + 15) / 16) * ((c->d.ny + 15) / 16);
 }
 
 // The 2D fused step tile.  16x8 tiles (up to two workgroups of four waves per
@@ -1375,8 +1388,15 @@ int dg_adjoint_forward(dg_ctx* c, const double* U0, double* UT, double dt, int32
     } else if (a[i].op == RV_ADVANCE) {
       // the last step of an advance that is stored writes straight into its slot
       const bool stored = i + 1 < split && a[i + 1].op == RV_STORE;
+      double* end = stored ? ckpt + (size_t)a[i + 1].a * n : work;
+      if (!stages) {
+        rc = advance(c, c->stream, state, end, dt, a[i].a);
+        cur += a[i].a;
+        state = end;
+        continue;
+      }
       for (int k = 0; k < a[i].a && rc == DG_OK; ++k, ++cur) {
-        double* dst = (stored && k == a[i].a - 1) ? ckpt + (size_t)a[i + 1].a * n : work;
+        double* dst = k == a[i].a - 1 ? end : work;
         rc = rk3_step_to(c, c->stream, state, dst, dt, S1(cur), S2(cur));
         state = dst;
       }
@@ -1389,11 +1409,12 @@ int dg_adjoint_forward(dg_ctx* c, const double* U0, double* UT, double dt, int32
   for (size_t i = split; i < a.size() && a[i].op != RV_ADJOINT; ++i)
     if (a[i].op == RV_ADVANCE) k0 += a[i].a;
   state = ckpt + (size_t)slot * n;
-  for (int k = 0; k < k0 + 1 && rc == DG_OK; ++k) {
-    const int step = nsteps - 1 - k0 + k;
-    rc = rk3_step_to(c, c->stream, state, UT, dt, k == k0 ? S1(step) : nullptr, k == k0 ? S2(step) : nullptr);
+  const int alone = stages ? k0 : k0 + 1;  // steps whose stage states are not kept
+  if (alone > 0) {
+    rc = advance(c, c->stream, state, UT, dt, alone);
     state = UT;
   }
+  if (rc == DG_OK && stages) rc = rk3_step_to(c, c->stream, state, UT, dt, S1(nsteps - 1), S2(nsteps - 1));
   return rc;
 }
 
@@ -1426,15 +1447,8 @@ int dg_adjoint_backward(dg_ctx* c, double dt, int32_t nsteps, int32_t nsnaps, do
         }
         break;
       case RV_ADVANCE:
-        // the first step out of a slot writes into the work buffer
-        for (int k = 0; k < a[i].a && rc == DG_OK; ++k) {
-          if (state != work) {
-            rc = rk3_step_to(c, c->stream, state, work, dt);
-            state = work;
-          } else {
-            rc = rk3_step(c, c->stream, work, dt);
-          }
-        }
+        rc = advance(c, c->stream, state, work, dt, a[i].a);
+        state = work;
         break;
       case RV_ADJOINT: {
         // lam <- (d step / d U^k)^T lam
