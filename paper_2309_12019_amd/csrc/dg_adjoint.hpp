@@ -49,9 +49,9 @@ struct ZRec {
   static_assert(SIZE == zrec_doubles(DIM, NL), "record layout");
 };
 
-template <int DIM, int P, int FLUX, int MODE, int S, int W, int SL>
+template <int DIM, int P, int FLUX, int MODE, int S, int W>
 struct AdjCell {
-  using C = Cell<DIM, P, FLUX, MODE, S, W, SL>;
+  using C = Cell<DIM, P, FLUX, MODE, S, W>;
   using TB = typename C::TB;
   using Z = ZRec<DIM, P>;
   static constexpr int N = P + 1;
@@ -447,8 +447,6 @@ struct AdjCell {
     constexpr int axis = F >> 1;
     constexpr bool plus = F & 1;
     const double s = plus ? 1.0 : -1.0;
-    const double* const bn = C::CELLS ? rebase(b, C::off(F)) : b + C::off(F);
-    const double* const bvn = C::CELLS ? rebase(bv, C::off(F)) : bv + C::off(F);
     double tm[N], tp[N], sm[N], sp[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) {
@@ -458,9 +456,9 @@ struct AdjCell {
         const int j = axis == 0 ? i + N * k : k + N * i;
         const double so = plus ? 1.0 : TB::dg.sgn[i];  // (sgn[0] = 1)
         const double sn = plus ? TB::dg.sgn[i] : 1.0;
-        const double cn = bn[j * S];
+        const double cn = b[j * S + C::off(F)];
         const double gf = sn * (P <= 2 ? A.lfac[i + N * k] : g2h * TB::dg.minv[i] * TB::dg.minv[k]);
-        const double vn = bvn[j * S];
+        const double vn = bv[j * S + C::off(F)];
         t = i == 0 ? c[j] : fma(so, c[j], t);
         tn = i == 0 ? cn : fma(sn, cn, tn);
         gt = i == 0 ? g[j] : fma(so, g[j], gt);
@@ -763,10 +761,8 @@ __device__ inline void load_cell_at(const StageArgs& A, const double* U, int gx,
 template <int DIM, int P, int FLUX, int MODE, int TX, int TY>
 __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX) adj_sensor_kernel(const AdjArgs Ad) {
   using G = TileGeom<DIM, TX, TY>;
-  constexpr int NL = DIM == 1 ? P + 1 : (P + 1) * (P + 1);
-  using LY = SlotLayout<DIM, NL, G::S>;
-  constexpr int S = LY::S, SL = LY::SL;
-  using AC = AdjCell<DIM, P, FLUX, MODE, S, G::W, SL>;
+  using AC = AdjCell<DIM, P, FLUX, MODE, G::S, G::W>;
+  constexpr int NL = AC::NL, S = G::S;
   extern __shared__ double lds[];
   const StageArgs& A = Ad.s;
   const int tile = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);  // XCD-aware order
@@ -778,16 +774,16 @@ __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX) adj_sensor_kernel(con
   const size_t cell = (size_t)gy * A.nx + gx;
   double c[NL], v[NL];
   load_cell<DIM, NL>(A, gx, gy, c);
-  if (halo) load_slot<DIM, NL, S, SL>(A, lds, hs, hgx, hgy);
+  if (halo) load_slot<DIM, NL, S>(A, lds, hs, hgx, hgy);
   if (active) {
 #pragma unroll
     for (int j = 0; j < NL; ++j) v[j] = Ad.v[cell * NL + j];
   }
 #pragma unroll
-  for (int j = 0; j < NL; ++j) lds[sc * SL + j * S] = c[j];
+  for (int j = 0; j < NL; ++j) lds[j * S + sc] = c[j];
   tile_barrier();
   if (!active) return;
-  AC::template sensor_adjoint<true>(A, lds + sc * SL, c, gx, gy, v, Ad.z + cell, (size_t)A.nx * (DIM == 2 ? A.ny : 1));
+  AC::template sensor_adjoint<true>(A, lds + sc, c, gx, gy, v, Ad.z + cell, (size_t)A.nx * (DIM == 2 ? A.ny : 1));
 }
 
 // Pass B kernel: J^T v and the combination.  LDS: 2 * NL * S doubles (state
@@ -795,12 +791,10 @@ __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX) adj_sensor_kernel(con
 template <int DIM, int P, int FLUX, int MODE, int TX, int TY>
 __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX) adj_grad_kernel(const AdjArgs Ad) {
   using G = TileGeom<DIM, TX, TY>;
-  constexpr int NL = DIM == 1 ? P + 1 : (P + 1) * (P + 1);
-  using LY = SlotLayout<DIM, NL, G::S>;
-  constexpr int S = LY::S, SL = LY::SL;
-  using AC = AdjCell<DIM, P, FLUX, MODE, S, G::W, SL>;
+  using AC = AdjCell<DIM, P, FLUX, MODE, G::S, G::W>;
+  constexpr int NL = AC::NL, S = G::S;
   extern __shared__ double lds[];
-  double* ldsv = lds + NL * G::S;
+  double* ldsv = lds + NL * S;
   const StageArgs& A = Ad.s;
   const int tile = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);  // XCD-aware order
   const int ix0 = (tile % gridDim.x) * TX, iy0 = DIM == 2 ? (tile / gridDim.x) * TY : 0;
@@ -814,27 +808,27 @@ __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX) adj_grad_kernel(const
   load_cell_v<DIM, NL>(Ad, gx, gy, v);
   if (halo) {
     double hv[NL];
-    load_slot<DIM, NL, S, SL>(A, lds, hs, hgx, hgy);
+    load_slot<DIM, NL, S>(A, lds, hs, hgx, hgy);
     load_cell_v<DIM, NL>(Ad, hgx, hgy, hv);
 #pragma unroll
-    for (int j = 0; j < NL; ++j) ldsv[hs * SL + j * S] = hv[j];
+    for (int j = 0; j < NL; ++j) ldsv[j * S + hs] = hv[j];
   }
 #pragma unroll
   for (int j = 0; j < NL; ++j) {
-    lds[sc * SL + j * S] = c[j];
-    ldsv[sc * SL + j * S] = v[j];
+    lds[j * S + sc] = c[j];
+    ldsv[j * S + sc] = v[j];
   }
   tile_barrier();
   if (!active) return;
   double Gr[NL];
-  AC::grad(Ad, lds + sc * SL, ldsv + sc * SL, c, v, gx, gy, cell, Gr);
+  AC::grad(Ad, lds + sc, ldsv + sc, c, v, gx, gy, cell, Gr);
   // the combination term by term over the whole cell, then one burst of
   // stores (loads of X and Y are not held behind stores to the same cell)
   double o[NL];
 #pragma unroll
   for (int j = 0; j < NL; ++j) {
     o[j] = Ad.beta * Gr[j];
-    if (Ad.alpha != 0.0) o[j] = fma(Ad.alpha, ldsv[sc * SL + j * S], o[j]);  // LDS: v is dead in registers by now
+    if (Ad.alpha != 0.0) o[j] = fma(Ad.alpha, ldsv[j * S + sc], o[j]);  // LDS: v is dead in registers by now
   }
   if (Ad.X) {
 #pragma unroll
@@ -859,12 +853,10 @@ __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX) adj_grad_kernel(const
 template <int DIM, int P, int FLUX, int MODE, int TX, int TY>
 __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX) adj_grad_sensor_kernel(const AdjArgs Ad) {
   using G = TileGeom<DIM, TX, TY>;
-  constexpr int NL = DIM == 1 ? P + 1 : (P + 1) * (P + 1);
-  using LY = SlotLayout<DIM, NL, G::S>;
-  constexpr int S = LY::S, SL = LY::SL;
-  using AC = AdjCell<DIM, P, FLUX, MODE, S, G::W, SL>;
+  using AC = AdjCell<DIM, P, FLUX, MODE, G::S, G::W>;
+  constexpr int NL = AC::NL, S = G::S;
   extern __shared__ double lds[];
-  double* ldsv = lds + NL * G::S;
+  double* ldsv = lds + NL * S;
   const StageArgs& A = Ad.s;
   const int tile = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);  // XCD-aware order
   const int ix0 = (tile % gridDim.x) * TX, iy0 = DIM == 2 ? (tile / gridDim.x) * TY : 0;
@@ -878,15 +870,15 @@ __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX) adj_grad_sensor_kerne
   load_cell_v<DIM, NL>(Ad, gx, gy, v);
   if (halo) {
     double hv[NL];
-    load_slot<DIM, NL, S, SL>(A, lds, hs, hgx, hgy);
+    load_slot<DIM, NL, S>(A, lds, hs, hgx, hgy);
     load_cell_v<DIM, NL>(Ad, hgx, hgy, hv);
 #pragma unroll
-    for (int j = 0; j < NL; ++j) ldsv[hs * SL + j * S] = hv[j];
+    for (int j = 0; j < NL; ++j) ldsv[j * S + hs] = hv[j];
   }
 #pragma unroll
   for (int j = 0; j < NL; ++j) {
-    lds[sc * SL + j * S] = c[j];
-    ldsv[sc * SL + j * S] = v[j];
+    lds[j * S + sc] = c[j];
+    ldsv[j * S + sc] = v[j];
   }
   // U' of the cell and of its halo slot, loaded now so that the loads
   // overlap pass B (up to P = 2; from P = 3 on the registers they would hold
@@ -901,11 +893,11 @@ __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX) adj_grad_sensor_kerne
   double o[NL];
   if (active) {
     double Gr[NL];
-    AC::grad(Ad, lds + sc * SL, ldsv + sc * SL, c, v, gx, gy, cell, Gr);
+    AC::grad(Ad, lds + sc, ldsv + sc, c, v, gx, gy, cell, Gr);
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
       o[j] = Ad.beta * Gr[j];
-      if (Ad.alpha != 0.0) o[j] = fma(Ad.alpha, ldsv[sc * SL + j * S], o[j]);
+      if (Ad.alpha != 0.0) o[j] = fma(Ad.alpha, ldsv[j * S + sc], o[j]);
     }
     if (Ad.X) {
 #pragma unroll
@@ -925,16 +917,16 @@ __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX) adj_grad_sensor_kerne
   }
   tile_barrier();  // every thread is done with the state plane
 #pragma unroll
-  for (int j = 0; j < NL; ++j) lds[sc * SL + j * S] = cn[j];
+  for (int j = 0; j < NL; ++j) lds[j * S + sc] = cn[j];
   if (halo) {
 #pragma unroll
-    for (int j = 0; j < NL; ++j) lds[hs * SL + j * S] = hn[j];
+    for (int j = 0; j < NL; ++j) lds[j * S + hs] = hn[j];
   }
   tile_barrier();
   // without the candidate barriers up to P = 2 (registers there are set by
   // pass B); from P = 3 on pass A would raise the register count
   if (active)
-    AC::template sensor_adjoint<(P > 2)>(A, lds + sc * SL, cn, gx, gy, o, Ad.znext + cell,
+    AC::template sensor_adjoint<(P > 2)>(A, lds + sc, cn, gx, gy, o, Ad.znext + cell,
                                          (size_t)A.nx * (DIM == 2 ? A.ny : 1));
 }
 

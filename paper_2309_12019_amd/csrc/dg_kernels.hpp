@@ -206,14 +206,6 @@ __device__ inline int opaque(int x) {
   return x;
 }
 
-// p + off as an address of its own: LDS instructions have no negative
-// immediate offsets, and the compiler would otherwise form the address of
-// every access (or pair of accesses) at a constant negative distance anew
-__device__ inline const double* rebase(const double* p, int off) {
-  asm("" : "+s"(off));
-  return p + off;
-}
-
 // XCD-aware tile order.  The dispatcher hands workgroup k (x fastest) to
 // XCD k mod 8, and each XCD has its own L2.  Workgroup k takes tile
 // xcd_tile(k, g) of the g tiles (row-major), a bijection under which every
@@ -267,23 +259,9 @@ __device__ inline double sqrt_pos(double x) {
   return fma(0.5 * rcp(s), e, s);
 }
 
-// LDS layout of a 2D tile's states: coefficient j of slot s at s * SL + j * S.
-// With an odd number of coefficients (P2: 9, P4: 25) a slot's coefficients are
-// consecutive (S = 1, SL = NL): lanes on consecutive slots still hit distinct
-// banks, and pairs of a slot's coefficients are one ds_read2 (512^2 P2 Burgers
-// gradient 117 -> 69 LDS reads, the whole gradient 4745 -> 4676 us; one-wave
-// stage kernels P2 108 -> 86 VGPRs, P4 254 -> 220, their times unchanged).
-// With an even number (P1, P3) the slots are consecutive in planes of the odd
-// stride PS, as in 1D.
-template <int DIM, int NL, int PS>
-struct SlotLayout {
-  static constexpr bool CELLS = DIM == 2 && NL % 2 == 1;
-  static constexpr int S = CELLS ? 1 : PS, SL = CELLS ? NL : 1;
-};
-
-// Per-cell arithmetic.  `b` points at this cell's coefficient 0 in LDS;
+// Per-cell arithmetic.  `b` points at this cell's slot in LDS plane 0;
 // coefficient j of the cell sits at b[j*S], of its face neighbour f at
-// b[j*S + off(f)] with off = SL times -1, +1, -W, +W (faces -x, +x, -y, +y).
+// b[j*S + off(f)] with off = -1, +1, -W, +W (faces -x, +x, -y, +y).
 // Non-periodic boundary slots hold the constant exterior state, so the
 // face traces need no special case.
 // Exact solution in R^2 of the four-quadrant Burgers problem of Sec. 5.4,
@@ -321,16 +299,15 @@ __device__ inline double riemann_exact(double x, double y, double t) {
   return w < d * (16.0 / 15.0) - 0.5 * t ? 0.5 : -1.0;
 }
 
-template <int DIM, int P, int FLUX, int MODE, int S, int W, int SL = 1>
+template <int DIM, int P, int FLUX, int MODE, int S, int W>
 struct Cell {
   using TB = Tables<DIM, P, FLUX>;
   static constexpr int N = P + 1;
   static constexpr int NL = TB::NL;
   static constexpr int Q = TB::Q;
   static constexpr int NF = 2 * DIM;
-  static constexpr bool CELLS = SL > 1;  // a slot's coefficients are consecutive
 
-  __device__ static constexpr int off(int f) { return SL * (f == 0 ? -1 : f == 1 ? 1 : f == 2 ? -W : W); }
+  __device__ static constexpr int off(int f) { return f == 0 ? -1 : f == 1 ? 1 : f == 2 ? -W : W; }
 
   // BC_RIEMANN exterior slots: a slot outside one boundary holds, in planes
   // 0..Q-1, the exact solution at the Q Gauss points of the one face that
@@ -425,7 +402,7 @@ struct Cell {
   template <int F>
   __device__ static inline void candidate(const double* b, double (&cd)[NL]) {
     constexpr int si = F & 1;
-    const double* const bn = CELLS ? rebase(b, off(F)) : b + off(F);
+    constexpr int o = off(F);
     cd[0] = 0.0;  // the constant coefficient is not used
     if constexpr (DIM == 1 || F < 2) {
       constexpr int R = DIM == 1 ? 1 : N;
@@ -433,7 +410,7 @@ struct Cell {
       for (int e = 0; e < R; ++e)
 #pragma unroll
         for (int a = 0; a < N; ++a) {
-          const double cn = bn[(a + N * e) * S];
+          const double cn = b[(a + N * e) * S + o];
 #pragma unroll
           for (int c = 0; c <= a; ++c)
             if (TB::dg.T[si][a][c] != 0.0 && (c + N * e) != 0)
@@ -444,7 +421,7 @@ struct Cell {
       for (int e = 0; e < N; ++e)
 #pragma unroll
         for (int a = 0; a < N; ++a) {
-          const double cn = bn[(a + N * e) * S];
+          const double cn = b[(a + N * e) * S + o];
 #pragma unroll
           for (int c = 0; c <= e; ++c)
             if (TB::dg.T[si][e][c] != 0.0 && (a + N * c) != 0)
@@ -788,8 +765,7 @@ struct Cell {
     const int axis = f >> 1;
     const int o = off(f);
     auto own = [&](int j) { return c[j]; };
-    const double* const bn = CELLS ? rebase(b, o) : b + o;
-    auto nbr = [&](int j) { return bn[j * S]; };
+    auto nbr = [&](int j) { return b[j * S + o]; };
     constexpr int NT_ = DIM == 2 ? N : 1;
     double tl[NT_], th[NT_];
     if (below) {
@@ -1266,13 +1242,13 @@ __device__ inline void load_cell(const StageArgs& A, int gx, int gy, double (&v)
   }
 }
 
-// Load one slot into the LDS tile.
-template <int DIM, int NL, int S, int SL = 1>
+// Load one slot into the coefficient-major LDS tile.
+template <int DIM, int NL, int S>
 __device__ inline void load_slot(const StageArgs& A, double* lds, int slot, int gx, int gy) {
   double v[NL];
   load_cell<DIM, NL>(A, gx, gy, v);
 #pragma unroll
-  for (int j = 0; j < NL; ++j) lds[slot * SL + j * S] = v[j];
+  for (int j = 0; j < NL; ++j) lds[j * S + slot] = v[j];
 }
 
 // The second combination of a cell's L, where the launch has one (A.out2)
@@ -1301,10 +1277,9 @@ __device__ inline void store_second(const StageArgs& A, size_t cell, const doubl
 template <int DIM, int P, int FLUX, int MODE, int TX, int TY, bool XBC = false, bool SECOND = false>
 __device__ inline void stage_tile(const StageArgs& A, double* lds, int ix0, int iy0) {
   using G = TileGeom<DIM, TX, TY>;
-  constexpr int NL = DIM == 1 ? P + 1 : (P + 1) * (P + 1);
-  using LY = SlotLayout<DIM, NL, G::S>;
-  constexpr int S = LY::S, SL = LY::SL;
-  using C = Cell<DIM, P, FLUX, MODE, S, G::W, SL>;
+  using C = Cell<DIM, P, FLUX, MODE, G::S, G::W>;
+  constexpr int NL = C::NL;
+  constexpr int S = G::S;
   const int nx = A.nx, ny = DIM == 2 ? A.ny : 1;
   const bool comb = !A.rhs_only && A.a != 0.0;
 
@@ -1326,18 +1301,18 @@ __device__ inline void stage_tile(const StageArgs& A, double* lds, int ix0, int 
         load_cell<DIM, NL>(A, hgx, hgy, v);
         C::riemann_slot(A, hgx, hgy, v);
 #pragma unroll
-        for (int j = 0; j < NL; ++j) lds[hs * SL + j * S] = v[j];
+        for (int j = 0; j < NL; ++j) lds[j * S + hs] = v[j];
       }
     }
   }
-  if (!xbc && halo) load_slot<DIM, NL, S, SL>(A, lds, hs, hgx, hgy);
+  if (!xbc && halo) load_slot<DIM, NL, S>(A, lds, hs, hgx, hgy);
 #pragma unroll
-  for (int j = 0; j < NL; ++j) lds[sc * SL + j * S] = c[j];
+  for (int j = 0; j < NL; ++j) lds[j * S + sc] = c[j];
   tile_barrier();
   constexpr bool SHARE = shares_faces(DIM, P, FLUX, TX, TY);
   using FG = FaceGeom<TX, TY>;
   constexpr int N = P + 1;
-  double* const fxl = lds + NL * G::S;      // shared x faces (SHARE)
+  double* const fxl = lds + NL * S;      // shared x faces (SHARE)
   double* const fyl = fxl + N * FG::XS;  // shared y faces
   if constexpr (SHARE) {
     // face phase: every x face of the tile, then every y face, one per
@@ -1352,8 +1327,8 @@ __device__ inline void stage_tile(const StageArgs& A, double* lds, int ix0, int 
       const int lo = face_slot<TX, TY>(axis, e, ix0, iy0, fgx, fgy);
       const int hi = lo + (axis == 0 ? 1 : G::W);
       double tl[N], th[N], v[C::Q], g[N];
-      C::template trace<false>(axis, [&](int j) { return lds[lo * SL + j * S]; }, tl);
-      C::template trace<true>(axis, [&](int j) { return lds[hi * SL + j * S]; }, th);
+      C::template trace<false>(axis, [&](int j) { return lds[j * S + lo]; }, tl);
+      C::template trace<true>(axis, [&](int j) { return lds[j * S + hi]; }, th);
       C::line_velocity(A, axis, opaque(axis == 0 ? fgy : fgx), v);
       bool xl = false, xh = false;
       if constexpr (XBC) {
@@ -1363,7 +1338,7 @@ __device__ inline void stage_tile(const StageArgs& A, double* lds, int ix0, int 
           xh = l == n - 1;
         }
       }
-      C::template face_moments<XBC, true>(axis, tl, th, v, xl, xh, lds + (xl ? lo : hi) * SL, g);
+      C::template face_moments<XBC, true>(axis, tl, th, v, xl, xh, lds + (xl ? lo : hi), g);
       double* dst = axis == 0 ? fxl + e : fyl + e;
 #pragma unroll
       for (int k = 0; k < N; ++k) dst[k * (axis == 0 ? FG::XS : FG::YS)] = g[k];
@@ -1380,10 +1355,10 @@ __device__ inline void stage_tile(const StageArgs& A, double* lds, int ix0, int 
     double L[NL];
     double* const gam_out = A.gamma ? A.gamma + cell : nullptr;
     if constexpr (SHARE) {
-      const double gam = C::template gamma_of<true>(A, lds + sc * SL, c, gx, gy);
+      const double gam = C::template gamma_of<true>(A, lds + sc, c, gx, gy);
       if (gam_out) *gam_out = gam;
       double R[NL], lam;
-      C::template residual<false, false>(A, lds + sc * SL, c, gx, gy, R, lam);
+      C::template residual<false, false>(A, lds + sc, c, gx, gy, R, lam);
       const int lx = t % TX, ly = t / TX;
       const int ex = ly * (TX + 1) + lx, ey = ly * TX + lx;
 #pragma unroll
@@ -1396,7 +1371,7 @@ __device__ inline void stage_tile(const StageArgs& A, double* lds, int ix0, int 
       }
       C::finish(A, c, gam, lam, R, L);
     } else {
-      C::template rhs<true, XBC>(A, lds + sc * SL, c, gx, gy, L, gam_out);
+      C::template rhs<true, XBC>(A, lds + sc, c, gx, gy, L, gam_out);
     }
     if constexpr (MODE != MODE_WENO) settle(L);
     double* dst = A.out + cell * NL;
@@ -1477,13 +1452,12 @@ template <int P, int FLUX, int MODE, bool XBC, bool SECOND>
 __device__ inline void roles_tile(const StageArgs& A, double* lds, int ix0, int iy0) {
   constexpr int TX = 8, TY = 8;
   using G = TileGeom<2, TX, TY>;
-  using LY = SlotLayout<2, (P + 1) * (P + 1), G::S>;
-  using C = Cell<2, P, FLUX, MODE, LY::S, G::W, LY::SL>;
+  using C = Cell<2, P, FLUX, MODE, G::S, G::W>;
   using FG = FaceGeom<TX, TY>;
-  constexpr int NL = C::NL, N = C::N, S = LY::S, SL = LY::SL;
+  constexpr int NL = C::NL, N = C::N, S = G::S;
   static_assert(FLUX == FLUX_LINADV || FLUX == FLUX_BURGERS, "the KPP flux has kpp_split_tile");
   static_assert(FG::NXF == 72 && FG::NYF == 72, "roles_face_task assumes 8 x 8 tiles");
-  double* const fxl = lds + NL * G::S;      // x faces
+  double* const fxl = lds + NL * S;      // x faces
   double* const fyl = fxl + N * FG::XS;  // y faces
   double* const gaml = fyl + N * FG::YS;  // gamma_e of the tile's cells
   const int nx = A.nx, ny = A.ny;
@@ -1505,24 +1479,24 @@ __device__ inline void roles_tile(const StageArgs& A, double* lds, int ix0, int 
           load_cell<2, NL>(A, hgx, hgy, v);
           C::riemann_slot(A, hgx, hgy, v);
 #pragma unroll
-          for (int j = 0; j < NL; ++j) lds[hs * SL + j * S] = v[j];
+          for (int j = 0; j < NL; ++j) lds[j * S + hs] = v[j];
         }
       }
     }
-    if (!xbc && halo) load_slot<2, NL, S, SL>(A, lds, hs, hgx, hgy);
+    if (!xbc && halo) load_slot<2, NL, S>(A, lds, hs, hgx, hgy);
 #pragma unroll
-    for (int j = 0; j < NL; ++j) lds[sc * SL + j * S] = c[j];
+    for (int j = 0; j < NL; ++j) lds[j * S + sc] = c[j];
   }
   tile_barrier();
   double R[NL], lam = 0.0;
   if (w == 0) {
-    if (active) C::template residual<false, false>(A, lds + sc * SL, c, gx, gy, R, lam);
+    if (active) C::template residual<false, false>(A, lds + sc, c, gx, gy, R, lam);
   } else if (w == 1) {
     if (active) {
       double cc[NL];
 #pragma unroll
-      for (int j = 0; j < NL; ++j) cc[j] = lds[sc * SL + j * S];
-      gaml[lc] = C::template gamma_of<true>(A, lds + sc * SL, cc, gx, gy);
+      for (int j = 0; j < NL; ++j) cc[j] = lds[j * S + sc];
+      gaml[lc] = C::template gamma_of<true>(A, lds + sc, cc, gx, gy);
     }
   } else {
     for (int i = t - 128; i < FG::NXF + FG::NYF; i += kRoleThreads - 128) {
@@ -1532,8 +1506,8 @@ __device__ inline void roles_tile(const StageArgs& A, double* lds, int ix0, int 
       const int lo = face_slot<TX, TY>(axis, e, ix0, iy0, fgx, fgy);
       const int hi = lo + (axis == 0 ? 1 : G::W);
       double tl[N], th[N], v[C::Q], g[N];
-      C::template trace<false>(axis, [&](int q) { return lds[lo * SL + q * S]; }, tl);
-      C::template trace<true>(axis, [&](int q) { return lds[hi * SL + q * S]; }, th);
+      C::template trace<false>(axis, [&](int q) { return lds[q * S + lo]; }, tl);
+      C::template trace<true>(axis, [&](int q) { return lds[q * S + hi]; }, th);
       C::line_velocity(A, axis, axis == 0 ? fgy : fgx, v);
       bool xl = false, xh = false;
       if constexpr (XBC) {
@@ -1543,7 +1517,7 @@ __device__ inline void roles_tile(const StageArgs& A, double* lds, int ix0, int 
           xh = l == n - 1;
         }
       }
-      C::template face_moments<XBC>(axis, tl, th, v, xl, xh, lds + (xl ? lo : hi) * SL, g);
+      C::template face_moments<XBC>(axis, tl, th, v, xl, xh, lds + (xl ? lo : hi), g);
       double* dst = axis == 0 ? fxl + e : fyl + e;
 #pragma unroll
       for (int k = 0; k < N; ++k) dst[k * (axis == 0 ? FG::XS : FG::YS)] = g[k];
@@ -1620,9 +1594,8 @@ template <int P, int MODE, int V0, int NTH, bool SECOND>
 __device__ inline void kpp_split_tile(const StageArgs& A, double* lds, int ix0, int iy0) {
   constexpr int TX = 8, TY = 8;
   using G = TileGeom<2, TX, TY>;
-  using LY = SlotLayout<2, (P + 1) * (P + 1), G::S>;
-  using C = Cell<2, P, FLUX_KPP, MODE, LY::S, G::W, LY::SL>;
-  constexpr int NL = C::NL, N = C::N, Q = C::Q, S = LY::S, SL = LY::SL;
+  using C = Cell<2, P, FLUX_KPP, MODE, G::S, G::W>;
+  constexpr int NL = C::NL, N = C::N, Q = C::Q, S = G::S;
   constexpr int NV = 64 * Q * Q;  // volume node tasks
   constexpr int NFA = 72;         // faces per axis ((TX + 1) TY = TX (TY + 1))
   constexpr int NFN = 2 * NFA * Q;  // face node tasks
@@ -1631,7 +1604,7 @@ __device__ inline void kpp_split_tile(const StageArgs& A, double* lds, int ix0, 
                 "split_vol_task and split_face_task assume 8 x 8 tiles");
   constexpr int H0 = 64;  // the first thread of the node tasks
   static_assert(NTH % 64 == 0 && NTH > H0, "whole waves, at least one for the node tasks");
-  double* const vol = lds + NL * G::S;
+  double* const vol = lds + NL * S;
   double* const fnl = vol + 2 * Q * Q * 64;
   const int nx = A.nx, ny = A.ny;
   const int t = threadIdx.x;
@@ -1643,16 +1616,16 @@ __device__ inline void kpp_split_tile(const StageArgs& A, double* lds, int ix0, 
     int hs, hgx, hgy;
     const bool halo = tile_slots<2, TX, TY>(t, ix0, iy0, sc, gx, gy, hs, hgx, hgy);
     load_cell<2, NL>(A, gx, gy, c);
-    if (halo) load_slot<2, NL, S, SL>(A, lds, hs, hgx, hgy);
+    if (halo) load_slot<2, NL, S>(A, lds, hs, hgx, hgy);
 #pragma unroll
-    for (int j = 0; j < NL; ++j) lds[sc * SL + j * S] = c[j];
+    for (int j = 0; j < NL; ++j) lds[j * S + sc] = c[j];
   }
   tile_barrier();
   auto vol_node = [&](int v) {
     int slot, qx, qy;
     const int o = split_vol_task(v, Q, slot, qx, qy);
     double s1[N];
-    C::xline([&](int j) { return lds[slot * SL + j * S]; }, qx, s1);
+    C::xline([&](int j) { return lds[j * S + slot]; }, qx, s1);
     double Fx, Fy;
     sincos_inl(C::ynode(s1, qy), &Fx, &Fy);
     vol[o] = Fx;
@@ -1661,7 +1634,7 @@ __device__ inline void kpp_split_tile(const StageArgs& A, double* lds, int ix0, 
   const bool active = owner && gx < nx && gy < ny;
   double gam = 0.0;
   if (owner) {
-    if (active) gam = C::template gamma_of<true>(A, lds + sc * SL, c, gx, gy);
+    if (active) gam = C::template gamma_of<true>(A, lds + sc, c, gx, gy);
     for (int k = 0; k < V0; ++k) vol_node(k * 64 + t);
   } else {
     const int u = t - H0;
@@ -1672,8 +1645,8 @@ __device__ inline void kpp_split_tile(const StageArgs& A, double* lds, int ix0, 
       const int lo = face_slot<TX, TY>(axis, e, ix0, iy0, fgx, fgy);
       const int hi = lo + (axis == 0 ? 1 : G::W);
       double tl[N], th[N];
-      C::template trace<false>(axis, [&](int q) { return lds[lo * SL + q * S]; }, tl);
-      C::template trace<true>(axis, [&](int q) { return lds[hi * SL + q * S]; }, th);
+      C::template trace<false>(axis, [&](int q) { return lds[q * S + lo]; }, tl);
+      C::template trace<true>(axis, [&](int q) { return lds[q * S + hi]; }, th);
       double ul, uh;
       C::face_node(tl, th, r, ul, uh);
       fnl[o] = C::template llf_kpp<true>(axis, ul, uh);
@@ -1684,7 +1657,7 @@ __device__ inline void kpp_split_tile(const StageArgs& A, double* lds, int ix0, 
   if (!active) return;
   double R[NL], lam;
   const int lc = t;
-  C::template residual<false, false, 64>(A, lds + sc * SL, c, gx, gy, R, lam, vol + lc);
+  C::template residual<false, false, 64>(A, lds + sc, c, gx, gy, R, lam, vol + lc);
 #pragma unroll
   for (int f = 0; f < 4; ++f) {
     const int axis = f >> 1;
@@ -1904,11 +1877,8 @@ __device__ inline void step_stage(const StageArgs& A, const double* tin, const d
   using G = StepGeom<DIM, TX, TY>;
   using TI = typename G::template T<KO + 1>;
   using TO = typename G::template T<KO>;
-  constexpr int NL = DIM == 1 ? P + 1 : (P + 1) * (P + 1);
-  using LI = SlotLayout<DIM, NL, TI::S>;    // input tile
-  using LO = SlotLayout<DIM, NL, TO::S>;    // output tile
-  using LA = SlotLayout<DIM, NL, G::A::S>;  // U^n
-  using C = Cell<DIM, P, FLUX, MODE, LI::S, TI::W, LI::SL>;
+  using C = Cell<DIM, P, FLUX, MODE, TI::S, TI::W>;
+  constexpr int NL = C::NL;
   // 2D: LDS allows one workgroup per CU, so up to P = 2 the registers freed
   // by the scheduling barrier do not raise the occupancy
   constexpr bool SB = DIM == 1 || P > 2;
@@ -1921,11 +1891,11 @@ __device__ inline void step_stage(const StageArgs& A, const double* tin, const d
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
       double v = b * fma(A.dt, L[j], c[j]);
-      if (a != 0.0) v = fma(a, ta[aslot * LA::SL + j * LA::S], v);
+      if (a != 0.0) v = fma(a, ta[j * G::A::S + aslot], v);
       if constexpr (KO == 0)
         A.out[((size_t)wy * nx + wx) * NL + j] = v;
       else
-        tout[o * LO::SL + j * LO::S] = v;
+        tout[j * TO::S + o] = v;
     }
   };
   // the slots of cell o; false if it has no equation (past a ragged edge, or
@@ -1939,7 +1909,7 @@ __device__ inline void step_stage(const StageArgs& A, const double* tin, const d
     if (!step_cell<DIM>(A, gx, gy, wx, wy)) {
       if (ext) {
 #pragma unroll
-        for (int j = 0; j < NL; ++j) tout[o * LO::SL + j * LO::S] = j == 0 ? A.bc : 0.0;
+        for (int j = 0; j < NL; ++j) tout[j * TO::S + o] = j == 0 ? A.bc : 0.0;
       }
       return false;
     }
@@ -1953,8 +1923,8 @@ __device__ inline void step_stage(const StageArgs& A, const double* tin, const d
       if (!locate(o, true, islot, aslot, wx, wy)) continue;
       double c[NL], L[NL];
 #pragma unroll
-      for (int j = 0; j < NL; ++j) c[j] = tin[islot * LI::SL + j * LI::S];
-      C::template rhs<SB>(A, tin + islot * LI::SL, c, wx, wy, L);
+      for (int j = 0; j < NL; ++j) c[j] = tin[j * TI::S + islot];
+      C::template rhs<SB>(A, tin + islot, c, wx, wy, L);
       store(o, aslot, wx, wy, c, L);
     }
   } else {
@@ -1967,15 +1937,15 @@ __device__ inline void step_stage(const StageArgs& A, const double* tin, const d
     double c[NL], R[NL], lam = 0.0;
     if (valid) {
 #pragma unroll
-      for (int j = 0; j < NL; ++j) c[j] = tin[islot * LI::SL + j * LI::S];
+      for (int j = 0; j < NL; ++j) c[j] = tin[j * TI::S + islot];
       if (role == 0) {
         double L[NL];
-        C::template rhs<SB>(A, tin + islot * LI::SL, c, wx, wy, L);
+        C::template rhs<SB>(A, tin + islot, c, wx, wy, L);
         store(o, aslot, wx, wy, c, L);
       } else if (role == 1) {
-        gx_lds[o - NF_] = C::template gamma_of<SB>(A, tin + islot * LI::SL, c, wx, wy);
+        gx_lds[o - NF_] = C::template gamma_of<SB>(A, tin + islot, c, wx, wy);
       } else {
-        C::residual(A, tin + islot * LI::SL, c, wx, wy, R, lam);
+        C::residual(A, tin + islot, c, wx, wy, R, lam);
       }
     }
     tile_barrier();  // every thread: gamma of the split cells is in LDS
@@ -1994,7 +1964,6 @@ template <int DIM, int P, int FLUX, int MODE, int TX, int TY>
 __global__ void __launch_bounds__(step_threads(DIM, TX, TY)) step_kernel(const StageArgs A) {
   using G = StepGeom<DIM, TX, TY>;
   constexpr int NL = DIM == 1 ? P + 1 : (P + 1) * (P + 1);
-  using LA = SlotLayout<DIM, NL, G::A::S>;
   extern __shared__ double lds[];
   double* ta = lds;
   double* tb = ta + NL * G::A::S;
@@ -2017,7 +1986,7 @@ __global__ void __launch_bounds__(step_threads(DIM, TX, TY)) step_kernel(const S
       for (int j = 0; j < NL; ++j) v[j] = j == 0 ? A.bc : 0.0;
     }
 #pragma unroll
-    for (int j = 0; j < NL; ++j) ta[o * LA::SL + j * LA::S] = v[j];
+    for (int j = 0; j < NL; ++j) ta[j * G::A::S + o] = v[j];
   }
   tile_barrier();
   step_stage<DIM, P, FLUX, MODE, TX, TY, 2>(A, ta, ta, tb, ix0, iy0, 0.0, 1.0, gx);
