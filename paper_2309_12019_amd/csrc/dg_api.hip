@@ -340,8 +340,10 @@ int line_steps(dg_ctx* c, hipStream_t st, double* U, double dt, int nsteps) {
     d[4] = dt * kB53 / kA53;
     d[5] = dt * kB54 / kA54;
   }
-  const bool one = c->d.nx <= kLineThreads;
-  const LinePlan p = line_plan(c->d.nx, c->nl, r.order, c->cus, one ? kLineChunk : (nsteps + 1) / 2);
+  const bool euler = c->d.flux == DG_FLUX_EULER;
+  LinePlan p = line_plan(c->d.nx, c->nl, r.order, c->cus, (nsteps + 1) / 2, euler);
+  const bool one = p.halo == 0;  // the whole mesh in one workgroup
+  if (one) p.steps = kLineChunk;
   r.threads = p.threads;
   r.line.own = p.own;
   int launches = (nsteps + p.steps - 1) / p.steps;

@@ -73,16 +73,14 @@ struct EulerCell {
   static constexpr int Q = TB::Q;
   static constexpr int S = G::S;
 
-  // Volume minus face terms for the three components, and lambda_e.
-  // b: the cell's slot in the LDS tile (plane j = k N + a); c[k][a]: own state.
-  __device__ static inline void residual(const StageArgs& A, const double* b, const double (&c)[3][N], int ix,
-                                         double (&R)[3][N], double& lam) {
+  // Volume terms int phi_a' F(u_h) of the three components (R[k][0] = 0) and
+  // lambda_e, from the cell's coefficients c[k][a]
+  __device__ static inline void volume(const double (&c)[3][N], double (&R)[3][N], double& lam) {
 #pragma unroll
     for (int k = 0; k < 3; ++k)
 #pragma unroll
       for (int a = 0; a < N; ++a) R[k][a] = 0.0;
     lam = 0.0;
-    // ---- volume  int phi_a' F(u_h)
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       double u[3];
@@ -103,35 +101,52 @@ struct EulerCell {
         for (int a = 1; a < N; ++a) R[k][a] = fma(TB::nd.D[a][q], wF, R[k][a]);
       }
     }
-    // ---- faces  - phi_a H . n at x_{e -/+ 1/2}
+  }
+
+  // LLF flux through face f (0: x_{e-1/2}, 1: x_{e+1/2}) along its outward
+  // normal.  b: the cell's slot in the LDS tile (plane j = k N + a).
+  __device__ static inline void face_flux(const StageArgs& A, const double* b, const double (&c)[3][N], int ix, int f,
+                                          double (&H)[3]) {
+    const bool wall = !A.per_x && (f ? ix == A.nx - 1 : ix == 0);
+    double um[3], up[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      double tm = 0.0, tp = 0.0;
+#pragma unroll
+      for (int a = 0; a < N; ++a) {
+        const double so = f ? 1.0 : TB::dg.sgn[a];  // P_a at this cell's face
+        const double sn = f ? TB::dg.sgn[a] : 1.0;  // P_a at the neighbour's face
+        tm = fma(so, c[k][a], tm);
+        tp = fma(sn, b[(k * N + a) * S + C::off(f)], tp);
+      }
+      um[k] = tm;
+      up[k] = tp;
+    }
+    if (wall) {
+      up[0] = um[0];
+      up[1] = -um[1];
+      up[2] = um[2];
+    }
+    llf_euler(f ? 1.0 : -1.0, um, up, H);
+  }
+
+  // - phi_a H . n of face f into R
+  __device__ static inline void add_face(int f, const double (&H)[3], double (&R)[3][N]) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int a = 0; a < N; ++a) R[k][a] = fma(f ? -1.0 : -TB::dg.sgn[a], H[k], R[k][a]);
+  }
+
+  // Volume minus face terms for the three components, and lambda_e
+  __device__ static inline void residual(const StageArgs& A, const double* b, const double (&c)[3][N], int ix,
+                                         double (&R)[3][N], double& lam) {
+    volume(c, R, lam);
 #pragma unroll
     for (int f = 0; f < 2; ++f) {
-      const bool wall = !A.per_x && (f ? ix == A.nx - 1 : ix == 0);
-      double um[3], up[3];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        double tm = 0.0, tp = 0.0;
-#pragma unroll
-        for (int a = 0; a < N; ++a) {
-          const double so = f ? 1.0 : TB::dg.sgn[a];  // P_a at this cell's face
-          const double sn = f ? TB::dg.sgn[a] : 1.0;  // P_a at the neighbour's face
-          tm = fma(so, c[k][a], tm);
-          tp = fma(sn, b[(k * N + a) * S + C::off(f)], tp);
-        }
-        um[k] = tm;
-        up[k] = tp;
-      }
-      if (wall) {
-        up[0] = um[0];
-        up[1] = -um[1];
-        up[2] = um[2];
-      }
       double H[3];
-      llf_euler(f ? 1.0 : -1.0, um, up, H);
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
-#pragma unroll
-        for (int a = 0; a < N; ++a) R[k][a] = fma(f ? -1.0 : -TB::dg.sgn[a], H[k], R[k][a]);
+      face_flux(A, b, c, ix, f, H);
+      add_face(f, H, R);
     }
   }
 };

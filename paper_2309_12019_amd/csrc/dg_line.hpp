@@ -31,6 +31,10 @@
 namespace dgk {
 
 constexpr int kLineThreads = 256;
+// The Euler system on few windows: kLineSplitCells cells on three times as
+// many threads, a cell's work on three of them (line_kernel's SPLIT)
+constexpr int kLineSplitCells = 128;
+constexpr int kLineSplitThreads = 3 * kLineSplitCells;
 
 // Coefficients of the SSP methods in the form out = a un + b (u + dt' L(u)).
 // The five-stage fourth-order method of Spiteri and Ruuth (Shu-Osher form
@@ -76,12 +80,25 @@ __host__ __device__ inline bool line_cell(const LineArgs& B, int tile, int t, in
 constexpr int kLineMaxHalo = 48;
 constexpr int kLineChunk = 128;  // steps per launch of a mesh of one workgroup
 constexpr double kLineFixed = 4.0, kLineEval = 0.14;
+//   The Euler system takes split windows while each has a compute unit of its
+// own (128 cells, halo <= 24).  Sod P2, per step, whole cells -> split: 128
+// cells 4.26 -> 3.85 us, 1000 cells 4.71 -> 4.20, 15000 cells 4.76 -> 4.29
+// (P1 3.44 -> 2.99 at 128, P4 6.43 -> 5.98); past that, windows share compute
+// units and whole cells are cheaper.
+constexpr int kLineSplitMaxHalo = 24;
 struct LinePlan {
   int threads, own, halo, steps;
+  bool split;
 };
-inline LinePlan line_plan(int nx, int nv, int order, int cus, int steps) {
-  if (nx <= kLineThreads) return {(nx + 63) / 64 * 64, nx, 0, steps};
+inline LinePlan line_plan(int nx, int nv, int order, int cus, int steps, bool euler) {
   const int ev = rk_evals(order);
+  if (euler) {
+    if (nx <= kLineSplitCells) return {kLineSplitThreads, nx, 0, steps, true};
+    const int s = steps < kLineSplitMaxHalo / ev ? steps : kLineSplitMaxHalo / ev;
+    const int own = kLineSplitCells - 2 * ev * s;
+    if ((nx + own - 1) / own <= cus) return {kLineSplitThreads, own, ev * s, s, true};
+  }
+  if (nx <= kLineThreads) return {(nx + 63) / 64 * 64, nx, 0, steps, false};
   LinePlan best{};
   double cost = 0.0;
   for (int s = 1; s <= kLineMaxHalo / ev && s <= steps; ++s) {
@@ -90,7 +107,7 @@ inline LinePlan line_plan(int nx, int nv, int order, int cus, int steps) {
     const double c = ev * kLineEval * nv * (load > 1.0 ? load : 1.0) + kLineFixed / s;
     if (s == 1 || c < cost) {
       cost = c;
-      best = {kLineThreads, own, ev * s, s};
+      best = {kLineThreads, own, ev * s, s, false};
     }
   }
   return best;
@@ -98,9 +115,9 @@ inline LinePlan line_plan(int nx, int nv, int order, int cus, int steps) {
 
 // dU/dt of one cell of a scalar flux, from its coefficients and the slots of
 // its neighbours
-template <int P, int FLUX, int MODE>
+template <int P, int FLUX, int MODE, int CELLS = kLineThreads>
 struct LineCell {
-  using G = TileGeom<1, kLineThreads, 1>;
+  using G = TileGeom<1, CELLS, 1>;
   using C = Cell<1, P, FLUX, MODE, G::S, G::W>;
   static constexpr int NV = P + 1, S = G::S;
   __device__ static inline void rhs(const StageArgs& A, const double* b, const double (&c)[NV], int ix,
@@ -109,9 +126,9 @@ struct LineCell {
   }
 };
 
-template <int P, int MODE>
-struct LineCell<P, FLUX_EULER, MODE> {
-  using E = EulerCell<P, MODE, kLineThreads>;
+template <int P, int MODE, int CELLS>
+struct LineCell<P, FLUX_EULER, MODE, CELLS> {
+  using E = EulerCell<P, MODE, CELLS>;
   using C = typename E::C;
   static constexpr int N = P + 1, NV = 3 * N, S = E::S;
   __device__ static inline void rhs(const StageArgs& A, const double* b, const double (&c)[NV], int ix,
@@ -131,17 +148,33 @@ struct LineCell<P, FLUX_EULER, MODE> {
   }
 };
 
-__host__ __device__ constexpr int line_lds_doubles(int nv) { return 2 * nv * TileGeom<1, kLineThreads, 1>::S; }
+// (two state buffers; split: and the exchange of nv + 2 planes)
+__host__ __device__ constexpr int line_lds_doubles(int nv, bool split) {
+  return split ? (2 * nv + nv + 2) * TileGeom<1, kLineSplitCells, 1>::S : 2 * nv * TileGeom<1, kLineThreads, 1>::S;
+}
 
 // Grid: ceil(nx / own) workgroups of at most kLineThreads threads (a multiple
 // of 64), LDS line_lds_doubles.
-template <int P, int FLUX, int MODE, int RK>
-__global__ void __launch_bounds__(kLineThreads) line_kernel(const LineArgs B) {
-  using LC = LineCell<P, FLUX, MODE>;
+// SPLIT (the Euler system): workgroups of kLineSplitThreads, three threads per
+// cell on different waves.  One holds the cell (its state, the faces, the
+// combination), one evaluates the volume terms and lambda_e, one gamma_e; the
+// last two read the cell from LDS and hand their results over in LDS, behind a
+// second barrier.  On a wave alone on its SIMD an FP64 instruction takes about
+// 2.5 ns however independent it is of its neighbours, so an evaluation takes
+// what its longest wave has, instead of what a cell has (641 instructions at
+// P2), and one more barrier.
+template <int P, int FLUX, int MODE, int RK, bool SPLIT = false>
+__global__ void __launch_bounds__(SPLIT ? kLineSplitThreads : kLineThreads) line_kernel(const LineArgs B) {
+  static_assert(!SPLIT || FLUX == FLUX_EULER, "the scalar fluxes' cells are too short to split");
+  using LC = LineCell<P, FLUX, MODE, SPLIT ? kLineSplitCells : kLineThreads>;
   constexpr int NV = LC::NV, S = LC::S;
   extern __shared__ double lds[];
   const StageArgs& A = B.s;
-  const int t = threadIdx.x;
+  const int t = SPLIT ? threadIdx.x % kLineSplitCells : threadIdx.x;
+  // 0: volume, 1: the cell's owner, 2: sensor (waves go to SIMDs in turn: the
+  // sensor's two share one with the volume's)
+  const int role = SPLIT ? threadIdx.x / kLineSplitCells : 1;
+  const bool owner = role == 1;
   int gx, wx = 0, wy;
   bool stores;
   const bool held = line_cell(B, xcd_tile(blockIdx.x, gridDim.x), t, gx, stores);
@@ -155,7 +188,7 @@ __global__ void __launch_bounds__(kLineThreads) line_kernel(const LineArgs B) {
   const bool ring = B.halo == 0 && A.per_x;
   // otherwise the slots beyond the workgroup's cells hold the exterior state
   // (only stale cells and the ends of a non-periodic mesh read them)
-  if (t < 2 && !ring) {
+  if (owner && t < 2 && !ring) {
     const int end = t == 0 ? 0 : (B.own + 2 * B.halo) + 1;
 #pragma unroll
     for (int k = 0; k < 2; ++k)
@@ -167,7 +200,7 @@ __global__ void __launch_bounds__(kLineThreads) line_kernel(const LineArgs B) {
   auto eval = [&](double (&L)[NV]) {
     double* const buf = lds + par * (NV * S);
     par ^= 1;
-    if (held) {
+    if (held && owner) {
 #pragma unroll
       for (int j = 0; j < NV; ++j) buf[j * S + t + 1] = c[j];
       if (ring && t == 0) {
@@ -180,7 +213,47 @@ __global__ void __launch_bounds__(kLineThreads) line_kernel(const LineArgs B) {
       }
     }
     tile_barrier();
-    if (active) LC::rhs(A, buf + t + 1, c, wx, L);
+    if constexpr (SPLIT) {
+      using E = typename LC::E;
+      constexpr int N = P + 1;
+      double* const ex = lds + 2 * NV * S + t;  // volume terms (planes 0 .. NV-1), lambda_e, gamma_e
+      double u[3][N], H[2][3];
+      if (active) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j) u[j / N][j % N] = owner ? c[j] : buf[j * S + t + 1];
+        if (role == 0) {
+          double R[3][N], lam;
+          E::volume(u, R, lam);
+#pragma unroll
+          for (int j = 0; j < NV; ++j)
+            if (j % N) ex[j * S] = R[j / N][j % N];
+          ex[NV * S] = lam;
+        } else if (role == 2) {
+          ex[(NV + 1) * S] = LC::C::template gamma_of<true>(A, buf + t + 1, u[0], wx, 0);
+        } else {
+#pragma unroll
+          for (int f = 0; f < 2; ++f) E::face_flux(A, buf + t + 1, u, wx, f, H[f]);
+        }
+      }
+      tile_barrier();
+      if (active && owner) {
+        double R[3][N];
+#pragma unroll
+        for (int j = 0; j < NV; ++j) R[j / N][j % N] = j % N ? ex[j * S] : 0.0;
+        const double lam = ex[NV * S], gam = ex[(NV + 1) * S];
+#pragma unroll
+        for (int f = 0; f < 2; ++f) E::add_face(f, H[f], R);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          double Lk[N];
+          LC::C::finish(A, u[k], gam, lam, R[k], Lk);
+#pragma unroll
+          for (int a = 0; a < N; ++a) L[k * N + a] = Lk[a];
+        }
+      }
+    } else {
+      if (active) LC::rhs(A, buf + t + 1, c, wx, L);
+    }
   };
   // v = a un + b (c + dt L), rounded as in the per-stage kernels (contraction
   // off: with a = 1 the compiler would fuse b (..) + un, which they do not)
@@ -192,39 +265,40 @@ __global__ void __launch_bounds__(kLineThreads) line_kernel(const LineArgs B) {
       v[j] = a != 0.0 ? fma(a, un[j], w) : w;
     }
   };
+  const bool mine = active && owner;
 #pragma unroll 1
   for (int s = 0; s < B.steps; ++s) {
     double L[NV];
 #pragma unroll
     for (int j = 0; j < NV; ++j) u0[j] = c[j];
     eval(L);
-    if (active) comb(0.0, 1.0, B.dts[0], L, u0, c);
+    if (mine) comb(0.0, 1.0, B.dts[0], L, u0, c);
     if constexpr (RK == 2) {
       eval(L);
-      if (active) comb(0.5, 0.5, B.dts[1], L, u0, c);
+      if (mine) comb(0.5, 0.5, B.dts[1], L, u0, c);
     } else if constexpr (RK == 3) {
       eval(L);
-      if (active) comb(0.75, 0.25, B.dts[1], L, u0, c);
+      if (mine) comb(0.75, 0.25, B.dts[1], L, u0, c);
       eval(L);
-      if (active) comb(1.0 / 3.0, 2.0 / 3.0, B.dts[2], L, u0, c);
+      if (mine) comb(1.0 / 3.0, 2.0 / 3.0, B.dts[2], L, u0, c);
     } else {
       double u2[NV], w[NV];
       eval(L);
-      if (active) comb(kA20, kA21, B.dts[1], L, u0, c);
+      if (mine) comb(kA20, kA21, B.dts[1], L, u0, c);
 #pragma unroll
       for (int j = 0; j < NV; ++j) u2[j] = c[j];
       eval(L);
-      if (active) comb(kA30, kA32, B.dts[2], L, u0, c);
+      if (mine) comb(kA30, kA32, B.dts[2], L, u0, c);
       eval(L);
-      if (active) {
+      if (mine) {
         comb(kA52, kA53, B.dts[4], L, u2, w);  // W = a52 U2 + a53 U3 + b53 dt L(U3)
         comb(kA40, kA43, B.dts[3], L, u0, c);
       }
       eval(L);
-      if (active) comb(1.0, kA54, B.dts[5], L, w, c);
+      if (mine) comb(1.0, kA54, B.dts[5], L, w, c);
     }
   }
-  if (active && stores) {
+  if (mine && stores) {
     double* const dst = A.out + (size_t)gx * NV;
 #pragma unroll
     for (int j = 0; j < NV; ++j) dst[j] = c[j];

@@ -316,11 +316,14 @@ hipError_t launch_euler(int mode, const StageArgs& A, hipStream_t s) {
 }
 
 // many steps of a 1D problem in one launch (line_kernel)
-template <int FLUX, int MODE, int RK>
+template <int FLUX, int MODE, int RK, bool SPLIT = false>
 hipError_t launch_line_fmr(const LaunchReq* r) {
   const LineArgs& B = r->line;
-  auto k = line_kernel<DGK_P, FLUX, MODE, RK>;
-  const size_t lds = sizeof(double) * (size_t)line_lds_doubles(LineCell<DGK_P, FLUX, MODE>::NV);
+  if constexpr (FLUX == FLUX_EULER && !SPLIT) {
+    if (r->threads == kLineSplitThreads) return launch_line_fmr<FLUX, MODE, RK, true>(r);
+  }
+  auto k = line_kernel<DGK_P, FLUX, MODE, RK, SPLIT>;
+  const size_t lds = sizeof(double) * (size_t)line_lds_doubles(LineCell<DGK_P, FLUX, MODE>::NV, SPLIT);
   if (lds > 65536) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -11,27 +11,30 @@ using namespace dgk;
 
 int main() {
   int bad = 0, launches = 0;
-  const int slots = TileGeom<1, kLineThreads, 1>::S;
   for (int nx : {1, 2, 63, 64, 65, 128, 255, 256, 257, 300, 511, 512, 1000, 4099, 65536, 70001, 1 << 20})
     for (int order : {2, 3, 4})
-      for (int nv : {2, 5, 15})
+      for (int nv : {2, 5, 6, 15})
         for (int steps : {1, 2, 5, 64})
           for (int per : {0, 1}) {
-            const LinePlan p = line_plan(nx, nv, order, 256, steps);
+            const bool euler = nv > 5;
+            const LinePlan p = line_plan(nx, nv, order, 256, steps, euler);
+            // cells a workgroup holds, its threads, its LDS slots
+            const int cells = p.split ? kLineSplitCells : kLineThreads;
+            const int slots = p.split ? TileGeom<1, kLineSplitCells, 1>::S : TileGeom<1, kLineThreads, 1>::S;
             LineArgs B{};
             B.s.nx = nx;
             B.s.ny = 1;
             B.s.per_x = per;
             B.own = p.own;
             B.halo = p.halo;
-            const bool one = nx <= kLineThreads;
+            const bool one = p.halo == 0;
             const int ev = rk_evals(order);
-            bad += p.threads % 64 != 0 || p.threads > kLineThreads || p.own < 1 || p.steps < 1 || p.steps > steps;
-            bad += p.own + 2 * p.halo > p.threads || (one ? p.halo != 0 || p.own != nx : p.halo != ev * p.steps);
+            bad += p.threads % 64 != 0 || p.threads != (p.split ? kLineSplitThreads : (one ? (nx + 63) / 64 * 64 : kLineThreads)) || (p.split && !euler) || p.own < 1 || p.steps < 1 || p.steps > steps;
+            bad += p.own + 2 * p.halo > cells || (one ? p.halo != 0 || p.own != nx : p.halo != ev * p.steps);
             std::vector<int> written(nx, 0);
             const int grid = (nx + p.own - 1) / p.own;
             for (int tile = 0; tile < grid; ++tile)
-              for (int t = 0; t < p.threads; ++t) {
+              for (int t = 0; t < (p.split ? cells : p.threads); ++t) {
                 int gx, wx, wy;
                 bool stores;
                 const bool held = line_cell(B, tile, t, gx, stores);

@@ -29,7 +29,8 @@ def _problem(kind, n, p, order, mode):
 # one workgroup: a cell, its wrap onto itself, wave and workgroup edges;
 # windows: one cell more than a workgroup, ragged last windows, and a mesh
 # with more windows than compute units (short launches)
-SIZES = [1, 2, 63, 64, 65, 256, 257, 400, 1000, 70001]
+# (the Euler system: one workgroup to 128 cells, split windows to 20480)
+SIZES = [1, 2, 63, 64, 65, 128, 129, 256, 257, 400, 1000, 20481, 70001]
 
 
 @pytest.mark.parametrize("n", SIZES)
