@@ -472,8 +472,16 @@ struct Cell {
     for (int f = 0; f < NF; ++f) {
       double cd[NL];
       cand_any<0>(f, b, cd);
-      const double wl = A.wnb * weight(A, qform(cd));  // (first, so that the choice is a select)
-      const double al = has[f] ? wl : 0.0;
+      double al = 0.0;
+      if constexpr (MODE == MODE_WENO1) {
+        const double wl = A.wnb * weight(A, qform(cd));  // (first, so that the choice is a select)
+        al = has[f] ? wl : 0.0;
+      } else {
+        // (as a select it raises the fused P2 step from 168 to 170 VGPRs, two
+        // workgroups of a 16x8 tile per CU instead of three: Burgers 512^2
+        // 44.6 -> 50.4 us per step, 384^2 30.6 -> 35.0)
+        al = has[f] ? A.wnb * weight(A, qform(cd)) : 0.0;
+      }
       asum += al;
 #pragma unroll
       for (int j = 1; j < NL; ++j) acc[j] = fma(al, cd[j], acc[j]);
@@ -698,8 +706,7 @@ struct Cell {
     for (int f = 0; f < NF; ++f) {
       double cd[NL];
       cand_any<0>(f, b, cd);
-      const double wl = A.wnb * weight(A, qform(cd));
-      al[f + 1] = has[f] ? wl : 0.0;
+      al[f + 1] = has[f] ? A.wnb * weight(A, qform(cd)) : 0.0;
       asum += al[f + 1];
       if constexpr (SB) __builtin_amdgcn_sched_barrier(0);
     }
@@ -1434,7 +1441,7 @@ __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX, stage_min_waves(DIM, 
 // XBC: the BC_RIEMANN exterior state compiled in (2D Burgers).
 constexpr int kRoleThreads = 256;
 // 8 x 8 tiles per compute unit up to which this kernel is taken: what its
-// registers (four waves; 64, 123, 228 and 352 VGPRs) let run side by side; at
+// registers (four waves; 60, 111, 194 and 307 VGPRs) let run side by side; at
 // P1 one, since there its second barrier costs more than the split gains; P2
 // with the exact exterior state (twice the instructions) three
 __host__ __device__ constexpr int roles_tiles_per_cu(int p, int bc_kind) {
