@@ -5,8 +5,8 @@
 A step is one SSP-RK3 step over the whole mesh of the workload: the three
 stages each evaluate the whole stabilised DG operator (traces, volume and face
 quadrature with the LLF flux, HWENO reconstruction, sensor, dissipation, mass
-inverse) and the RK combination.  K steps run as one dg_run call (HIP graph
-replay) with the state already resident in HBM; the timed region is bracketed
+inverse) and the RK combination.  K steps run as one dg_run call (in 2D a HIP
+graph replay, in 1D launches of many steps) with the state already resident in HBM; the timed region is bracketed
 by device synchronisation.  The default workload is 1024^2 P2 periodic 2D
 Burgers with seeded Fourier data, time step CFL h / ((2p+1) lambda_max(U^0))
 from the library's dg_stable_dt; dg_run takes the per-stage kernel there
@@ -75,7 +75,7 @@ def workload(name):
 # (rocprofv3 SQ_INSTS_VALU_{FMA,ADD,MUL,TRANS}_F64 per wave, one lane per
 # cell, FMA counted twice; profiles/stage_kernel_hbm_counters.md): the
 # per-unit figure of the arithmetic roofline.  Keyed by (dim, p, flux, mode).
-FLOPS_PER_CELL_STAGE = {(2, 2, 0, 2): 990.0, (2, 3, 0, 2): 2118.0, (2, 2, 1, 2): 1026.0, (1, 2, 3, 2): 832.0}
+FLOPS_PER_CELL_STAGE = {(2, 2, 0, 2): 990.0, (2, 3, 0, 2): 2138.0, (2, 2, 1, 2): 1026.0, (1, 2, 3, 2): 776.0}
 FP64_PEAK_TFLOPS = 78.6
 
 
@@ -83,15 +83,14 @@ def stage_bytes_per_dof(rk_order=3):
     """Algorithmic HBM bytes per DOF per stage launch: the first stage reads
     U^n and writes U^(1) (16 B); every later launch also reads the state it
     combines with (24 B).  Three-stage method: mean 64/3 B; two-stage: 20 B;
-    five-stage fourth-order (six launches): 136/6 B."""
-    launches = LAUNCHES_PER_STEP[rk_order]
-    return (16.0 + 24.0 * (launches - 1)) / launches
+    five-stage fourth-order: the fourth launch also forms the fifth's
+    combination (reads U^(2), writes its part: 16 B more), 128/5 B."""
+    launches = STAGES_PER_STEP[rk_order]
+    return (16.0 + 24.0 * (launches - 1) + (16.0 if rk_order == 4 else 0.0)) / launches
 
 
-# RK stages and stage-kernel launches per step of each SSP method (the
-# five-stage method evaluates the operator at U^(3) twice)
+# RK stages, and stage-kernel launches in 2D, per step of each SSP method
 STAGES_PER_STEP = {2: 2, 3: 3, 4: 5}
-LAUNCHES_PER_STEP = {2: 2, 3: 3, 4: 6}
 
 
 def prepare(w, fused=None):
@@ -113,14 +112,14 @@ def prepare(w, fused=None):
 def time_gpu(w, steps, warmup, fused=None, g=None, U0=None):
     """Time `steps` SSP steps (the workload's order) of dg_run; fused: None
     keeps the library's automatic choice of the fused step kernel, 0 / 1
-    forces it off / on."""
+    forces it off / on (in 1D, None and 1 run many steps per launch)."""
     import torch
     if g is None:
         g, U0 = prepare(w, fused)
     elif fused is not None:
         g.set_fused(fused)
     dt = w.dt()
-    # dg_run replays graphs cached per (state buffer, dt, chunk length): one
+    # in 2D dg_run replays graphs cached per (state buffer, dt, chunk length): one
     # untimed call of the timed length on the timed buffer records them, so
     # the timed region holds no capture or instantiation
     U = U0.clone()
@@ -459,21 +458,26 @@ def copy_probe(mib):
 def stage_kernel_name(w, tile):
     """The per-stage kernel the library launches for this workload and tile
     (2D 8x8: KPP spreads each tile over several waves; the other fluxes take
-    four-wave tiles up to three 8x8 tiles per compute unit)."""
+    four-wave tiles up to a number of 8x8 tiles per compute unit).  Kernel
+    mode 4: the sensor with the paper's exponents (16x16 tiles of the linear
+    flux at P2, and of P1, keep the general sensor's, 2)."""
+    mode = 4 if w.mode == 2 and w.q == 1.0 and w.r == 2.0 else w.mode
     if w.flux == 3:
-        return f"euler_stage_kernel<{w.p},{w.mode}>"
+        return f"euler_stage_kernel<{w.p},{mode}>"
     if w.dim == 1:
-        return f"stage_kernel<1,{w.p},{w.flux},{w.mode},{tile[0]},1>"
+        return f"stage_kernel<1,{w.p},{w.flux},{mode},{tile[0]},1>"
     tx, ty = tile
     if (tx, ty) == (8, 8):
         if w.flux == 2:
-            return f"kpp_split_kernel<{w.p},{w.mode}> (8x8)"
+            return f"kpp_split_kernel<{w.p},{mode}> (8x8)"
         import torch
         cus = torch.cuda.get_device_properties(0).multi_processor_count
         t8 = ((w.nx + 7) // 8) * ((w.ny + 7) // 8)
-        if t8 <= 3 * cus:
-            return f"roles_kernel<{w.p},{w.flux},{w.mode}> (8x8, four waves)"
-    return f"stage_kernel<{w.dim},{w.p},{w.flux},{w.mode},{tx},{ty}>"
+        if t8 <= {2: 3 if w.bc_kind == 1 else 4, 3: 2}.get(w.p, 1) * cus:
+            return f"roles_kernel<{w.p},{w.flux},{mode}> (8x8, four waves)"
+    elif mode == 4 and (w.p == 1 or (w.p == 2 and w.flux == 0)):
+        mode = 2
+    return f"stage_kernel<{w.dim},{w.p},{w.flux},{mode},{tx},{ty}>"
 
 
 def stage_roofline(w, wname, sec, launches, copy_gbs=None, tile=(16, 16)):
@@ -527,6 +531,22 @@ def fused_roofline(w, wname, sec, steps, step_tile=None):
             "hbm_frac": 16.0 * w.ndof / avg / 1e9 / HBM_PEAK_GBS}
 
 
+def line_roofline(w, sec, steps):
+    """The 1D kernel that advances windows of cells by many steps in one
+    launch: FP64 rate from the per-stage kernel's executed flops per cell
+    (the windows' recomputed halos not counted) against the FP64 vector peak.
+    A state passes through HBM once per launch of several steps."""
+    key = (w.dim, w.p, w.flux, w.mode)
+    avg = sec / steps
+    flops = 3.0 * FLOPS_PER_CELL_STAGE[key] * w.ncells if key in FLOPS_PER_CELL_STAGE else None
+    ach = flops / avg / 1e12 if flops else None
+    mode = 4 if w.mode == 2 and w.q == 1.0 and w.r == 2.0 else w.mode
+    return {"bound": "alu", "achieved": ach, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
+            "frac": ach / FP64_PEAK_TFLOPS if ach else None, "traffic": None,
+            "kernel": f"line_kernel<{w.p},{w.flux},{mode},{w.rk_order}> (many steps per launch)",
+            "flops_per_step": flops, "us_per_step": avg * 1e6}
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -567,10 +587,12 @@ def main():
     r = time_gpu(w, args.steps, args.warmup, g=g, U0=U0)
     sec = r["event_ms"] / 1e3
     dof_rate = STAGES_PER_STEP[w.rk_order] * w.ndof * args.steps / sec
-    if r["fused"]:
+    if w.dim == 1:
+        roof = line_roofline(w, sec, args.steps)
+    elif r["fused"]:
         roof = fused_roofline(w, args.workload, sec, args.steps, r["step_tile"])
     else:
-        roof = stage_roofline(w, args.workload, sec, LAUNCHES_PER_STEP[w.rk_order] * args.steps, cgbs, r["tile"])
+        roof = stage_roofline(w, args.workload, sec, STAGES_PER_STEP[w.rk_order] * args.steps, cgbs, r["tile"])
     del g, U0
     torch.cuda.empty_cache()
     line = {
@@ -604,15 +626,20 @@ def main():
         re_ = time_gpu(we, k, 5, g=ge, U0=Ue)
         s_ = re_["event_ms"] / 1e3
         ko = we.rk_order
-        launches = k if re_["fused"] else LAUNCHES_PER_STEP[ko] * k
+        launches = k if re_["fused"] else STAGES_PER_STEP[ko] * k
         ex = {"value": STAGES_PER_STEP[ko] * we.ndof * k / s_, "steps": k, "dofs": we.ndof,
               "rk_order": ko, "fused_step": re_["fused"], "tile": list(re_["tile"]),
-              "us_per_step": s_ / k * 1e6, "avg_launch_us": s_ / launches * 1e6}
-        if re_["fused"]:
-            ex["step_tile"] = list(re_["step_tile"])
-            ex["roofline"] = fused_roofline(we, name, s_, k, re_["step_tile"])
+              "us_per_step": s_ / k * 1e6}
+        if we.dim == 2:
+            ex["avg_launch_us"] = s_ / launches * 1e6
+        if we.dim == 1 or re_["fused"]:
+            if we.dim == 1:
+                ex["roofline"] = line_roofline(we, s_, k)
+            else:
+                ex["step_tile"] = list(re_["step_tile"])
+                ex["roofline"] = fused_roofline(we, name, s_, k, re_["step_tile"])
             rs = time_gpu(we, k, 5, fused=0, g=ge, U0=Ue)
-            ex["per_stage"] = stage_roofline(we, name, rs["event_ms"] / 1e3, LAUNCHES_PER_STEP[ko] * k, cgbs,
+            ex["per_stage"] = stage_roofline(we, name, rs["event_ms"] / 1e3, STAGES_PER_STEP[ko] * k, cgbs,
                                              rs["tile"])
             ex["per_stage"]["value"] = STAGES_PER_STEP[ko] * we.ndof * k / (rs["event_ms"] / 1e3)
         else:
