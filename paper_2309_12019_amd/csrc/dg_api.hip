@@ -208,7 +208,7 @@ int stage(dg_ctx* c, hipStream_t st, const double* uin, const double* un, double
     if (c->d.flux == DG_FLUX_KPP)
       r.waves = dgk::split_waves(t8, c->cus, c->d.p);
     else
-      r.waves = t8 <= (long long)dgk::roles_tiles_per_cu(c->d.p, c->d.bc_kind) * c->cus ? 4 : 1;
+      r.waves = t8 <= (long long)dgk::roles_tiles_per_cu(c->d.p, r.mode, c->d.bc_kind) * c->cus ? 4 : 1;
   }
   r.args.uin = uin;
   r.args.un = un;

@@ -1440,12 +1440,19 @@ __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX, stage_min_waves(DIM, 
 // same order as stage_tile, so the same result bit for bit.
 // XBC: the BC_RIEMANN exterior state compiled in (2D Burgers).
 constexpr int kRoleThreads = 256;
-// 8 x 8 tiles per compute unit up to which this kernel is taken: what its
-// registers (four waves; 60, 111, 194 and 307 VGPRs) let run side by side; at
-// P1 one, since there its second barrier costs more than the split gains; P2
-// with the exact exterior state (twice the instructions) three
-__host__ __device__ constexpr int roles_tiles_per_cu(int p, int bc_kind) {
-  return p == 2 ? (bc_kind == BC_RIEMANN ? 3 : 4) : p == 3 ? 2 : 1;
+// 8 x 8 tiles per compute unit up to which this kernel is taken.  The sensor
+// with the paper's exponents: what its registers (four waves; 60, 111, 194 and
+// 307 VGPRs) let run side by side, at P1 one, since there its second barrier
+// costs more than the split gains, and three at P2 with the exact exterior
+// state (twice the instructions).  The other modes, per ten second-order steps
+// of rotation, here against one-wave tiles: Zhao P1 150^2 99 / 105 us, P3 200^2
+// 190 / 216, P4 150^2 207 / 243, 200^2 327 / 291; LO P1 150^2 89 / 83, P2 240^2
+// 139 / 132, P3 200^2 172 / 177, P4 150^2 181 / 187, 200^2 275 / 236.
+__host__ __device__ constexpr int roles_tiles_per_cu(int p, int mode, int bc_kind) {
+  if (mode == MODE_WENO) return 3;
+  if (mode == MODE_WENO1) return p == 2 ? (bc_kind == BC_RIEMANN ? 3 : 4) : p == 3 ? 2 : 1;
+  if (p == 2) return mode == MODE_ZHAO && bc_kind != BC_RIEMANN ? 4 : 3;
+  return p == 1 ? (mode == MODE_ZHAO ? 3 : 1) : p == 3 ? 3 : 2;
 }
 __host__ __device__ inline int roles_lds_doubles(int nl, int n) {
   return tile_lds_doubles(2, nl, 8, 8) + face_lds_doubles(n, 8, 8) + 64;
