@@ -341,18 +341,15 @@ int line_steps(dg_ctx* c, hipStream_t st, double* U, double dt, int nsteps) {
     d[5] = dt * kB54 / kA54;
   }
   const bool euler = c->d.flux == DG_FLUX_EULER;
-  LinePlan p = line_plan(c->d.nx, c->nl, r.order, c->cus, (nsteps + 1) / 2, euler);
+  const LinePlan p = line_plan(c->d.nx, c->nl, r.order, c->cus, nsteps, euler);
   const bool one = p.halo == 0;  // the whole mesh in one workgroup
-  if (one) p.steps = kLineChunk;
   r.threads = p.threads;
   r.line.own = p.own;
-  int launches = (nsteps + p.steps - 1) / p.steps;
-  if (!one) launches += launches & 1;
+  const long long launches = line_launches(p, nsteps);
   double* cur = U;
   double* other = one ? U : c->U1;
-  for (int k = 0; k < launches; ++k) {
-    // the steps spread evenly over the launches
-    r.line.steps = (int)((long long)nsteps * (k + 1) / launches - (long long)nsteps * k / launches);
+  for (long long k = 0; k < launches; ++k) {
+    r.line.steps = line_launch_steps(nsteps, launches, k);
     r.line.halo = one ? 0 : rk_evals(r.order) * r.line.steps;
     r.line.s.uin = cur;
     r.line.s.out = other;

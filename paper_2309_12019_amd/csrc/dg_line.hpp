@@ -68,7 +68,8 @@ __host__ __device__ inline bool line_cell(const LineArgs& B, int tile, int t, in
   return t < B.own + 2 * B.halo;
 }
 
-// Launch shape for a mesh of nx cells and (at most) `steps` steps per launch.
+// Launch shape for a mesh of nx cells and a run of nsteps steps (every count of
+// the type).
 // Up to kLineThreads cells: one workgroup, any number of steps.  Beyond:
 // windows of kLineThreads threads, and as many steps per launch as pay.  A
 // longer launch hides more of a launch's fixed time (kLineFixed: the gap to
@@ -90,15 +91,16 @@ struct LinePlan {
   int threads, own, halo, steps;
   bool split;
 };
-inline LinePlan line_plan(int nx, int nv, int order, int cus, int steps, bool euler) {
+inline LinePlan line_plan(int nx, int nv, int order, int cus, int nsteps, bool euler) {
   const int ev = rk_evals(order);
+  const int steps = nsteps / 2 + nsteps % 2;  // windows alternate between two arrays: two launches at least
   if (euler) {
-    if (nx <= kLineSplitCells) return {kLineSplitThreads, nx, 0, steps, true};
+    if (nx <= kLineSplitCells) return {kLineSplitThreads, nx, 0, kLineChunk, true};
     const int s = steps < kLineSplitMaxHalo / ev ? steps : kLineSplitMaxHalo / ev;
     const int own = kLineSplitCells - 2 * ev * s;
     if ((nx + own - 1) / own <= cus) return {kLineSplitThreads, own, ev * s, s, true};
   }
-  if (nx <= kLineThreads) return {(nx + 63) / 64 * 64, nx, 0, steps, false};
+  if (nx <= kLineThreads) return {(nx + 63) / 64 * 64, nx, 0, kLineChunk, false};
   LinePlan best{};
   double cost = 0.0;
   for (int s = 1; s <= kLineMaxHalo / ev && s <= steps; ++s) {
@@ -111,6 +113,17 @@ inline LinePlan line_plan(int nx, int nv, int order, int cus, int steps, bool eu
     }
   }
   return best;
+}
+
+// Launches of a run of nsteps steps (an even number of them where they
+// alternate between two arrays), and the steps of launch k: spread evenly
+inline long long line_launches(const LinePlan& p, int nsteps) {
+  long long n = nsteps / p.steps + (nsteps % p.steps != 0);
+  if (p.halo > 0) n += n & 1;
+  return n;
+}
+inline int line_launch_steps(int nsteps, long long launches, long long k) {
+  return (int)(nsteps * (k + 1) / launches - nsteps * k / launches);
 }
 
 // dU/dt of one cell of a scalar flux, from its coefficients and the slots of

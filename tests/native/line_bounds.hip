@@ -1,7 +1,8 @@
 // Host-only check of line_kernel's windows: every mesh cell is stored by
 // exactly one thread, the loads and LDS slots stay inside their buffers, and
 // a stored cell is further from the window's ends than the launch has
-// operator evaluations.
+// operator evaluations; and the steps of a run's launches add up to the run,
+// for step counts up to the type's largest.
 #include <cstdio>
 #include <vector>
 
@@ -14,10 +15,10 @@ int main() {
   for (int nx : {1, 2, 63, 64, 65, 128, 255, 256, 257, 300, 511, 512, 1000, 4099, 65536, 70001, 1 << 20})
     for (int order : {2, 3, 4})
       for (int nv : {2, 5, 6, 15})
-        for (int steps : {1, 2, 5, 64})
+        for (int nsteps : {2, 3, 4, 9, 10, 128})
           for (int per : {0, 1}) {
             const bool euler = nv > 5;
-            const LinePlan p = line_plan(nx, nv, order, 256, steps, euler);
+            const LinePlan p = line_plan(nx, nv, order, 256, nsteps, euler);
             // cells a workgroup holds, its threads, its LDS slots
             const int cells = p.split ? kLineSplitCells : kLineThreads;
             const int slots = p.split ? TileGeom<1, kLineSplitCells, 1>::S : TileGeom<1, kLineThreads, 1>::S;
@@ -29,7 +30,7 @@ int main() {
             B.halo = p.halo;
             const bool one = p.halo == 0;
             const int ev = rk_evals(order);
-            bad += p.threads % 64 != 0 || p.threads != (p.split ? kLineSplitThreads : (one ? (nx + 63) / 64 * 64 : kLineThreads)) || (p.split && !euler) || p.own < 1 || p.steps < 1 || p.steps > steps;
+            bad += p.threads % 64 != 0 || p.threads != (p.split ? kLineSplitThreads : (one ? (nx + 63) / 64 * 64 : kLineThreads)) || (p.split && !euler) || p.own < 1 || p.steps < 1 || (p.halo > 0 && p.steps > (nsteps + 1) / 2);
             bad += p.own + 2 * p.halo > cells || (one ? p.halo != 0 || p.own != nx : p.halo != ev * p.steps);
             std::vector<int> written(nx, 0);
             const int grid = (nx + p.own - 1) / p.own;
@@ -56,6 +57,35 @@ int main() {
             for (int e = 0; e < nx; ++e) bad += written[e] != 1;
             ++launches;
           }
+  // launches of a run: at least one, at most the plan's steps each (so that no
+  // cell a window stores goes stale), all the steps in total, an even number
+  // where they alternate between two arrays
+  for (int nx : {1, 64, 256, 1000, 70001, 1 << 20})
+    for (int order : {2, 3, 4})
+      for (int nv : {2, 5, 6, 15})
+        for (int nsteps : {2, 3, 5, 15, 16, 17, 127, 128, 129, 1000, 65537, 1 << 30, 2147483519, 2147483520, 2147483600,
+                           2147483646, 2147483647}) {
+          const LinePlan p = line_plan(nx, nv, order, 256, nsteps, nv > 5);
+          const long long n = line_launches(p, nsteps);
+          const bool bounds = p.own >= 1 && p.steps >= 1 && n >= 1 && (p.halo == 0 || n % 2 == 0) &&
+                              (p.halo == 0 || p.halo == rk_evals(order) * p.steps);
+          bad += !bounds;
+          if (!bounds) {
+            std::printf("nx %d order %d nv %d: %d steps in %lld launches of %d (own %d)\n", nx, order, nv, nsteps, n,
+                        p.steps, p.own);
+            continue;
+          }
+          long long sum = 0;
+          const long long stride = n < 100000 ? 1 : n / 50000;  // (of very many launches, groups spread over the run)
+          for (long long k = 0; k < n; k += stride) {
+            const int s = line_launch_steps(nsteps, n, k);
+            bad += s < 0 || s > p.steps;
+            if (stride == 1) sum += s;
+          }
+          if (stride == 1) bad += sum != nsteps;
+          bad += line_launch_steps(nsteps, n, n - 1) > p.steps || line_launch_steps(nsteps, n, 0) > p.steps;
+          ++launches;
+        }
   std::printf("%d launches, %d failures\n", launches, bad);
   return bad ? 1 : 0;
 }
