@@ -314,13 +314,21 @@ int ssp_step(dg_ctx* c, hipStream_t st, double* U, double dt, double t) {
   return rk3_step_to(c, st, U, U, dt, nullptr, nullptr, t);
 }
 
+// the state that an odd number of alternating launches left in `from`, into U
+int copy_back(dg_ctx* c, hipStream_t st, double* U, const double* from) {
+  const hipError_t e =
+      hipMemcpyAsync(U, from, sizeof(double) * (size_t)c->ncells * c->nl, hipMemcpyDeviceToDevice, st);
+  return e == hipSuccess ? DG_OK : hip_fail(e, "step copy");
+}
+
 // Whether runs take the 1D kernel of many steps per launch (line_kernel): any
 // order, except where the fused step kernels are switched off.
 bool uses_line(const dg_ctx* c) { return c->d.dim == 1 && c->fused_mode != 0; }
 
 // nsteps >= 2 steps of a 1D problem on U in place.  A mesh of one workgroup
 // is updated in place; otherwise the launches alternate between U and U1
-// (windows read their neighbours' cells), an even number of them.
+// (windows read their neighbours' cells), an odd number of them followed by a
+// copy back into U.
 int line_steps(dg_ctx* c, hipStream_t st, double* U, double dt, int nsteps) {
   using namespace dgk;
   LaunchReq r{};
@@ -357,7 +365,7 @@ int line_steps(dg_ctx* c, hipStream_t st, double* U, double dt, int nsteps) {
     if (e != hipSuccess) return hip_fail(e, "line kernel launch");
     std::swap(cur, other);
   }
-  return DG_OK;
+  return cur == U ? DG_OK : copy_back(c, st, U, cur);
 }
 
 // len SSP steps on U in place.  With the fused kernel (three-stage method
@@ -379,11 +387,7 @@ int rk_steps(dg_ctx* c, hipStream_t st, double* U, double dt, int len, double t0
     if (rc) return rc;
     std::swap(cur, other);
   }
-  if (cur != U) {
-    hipError_t e = hipMemcpyAsync(U, cur, sizeof(double) * (size_t)c->ncells * c->nl, hipMemcpyDeviceToDevice, st);
-    if (e != hipSuccess) return hip_fail(e, "step copy");
-  }
-  return DG_OK;
+  return cur == U ? DG_OK : copy_back(c, st, U, cur);
 }
 
 int validate(const dg_mesh_desc* d) {

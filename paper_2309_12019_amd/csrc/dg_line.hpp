@@ -115,11 +115,13 @@ inline LinePlan line_plan(int nx, int nv, int order, int cus, int nsteps, bool e
   return best;
 }
 
-// Launches of a run of nsteps steps (an even number of them where they
-// alternate between two arrays), and the steps of launch k: spread evenly
+// Launches of a run of nsteps steps and the steps of launch k: spread evenly,
+// one at least.  Where they alternate between two arrays their number is even,
+// so that the last one writes the caller's, unless there is no step left for
+// another launch (one step each, an odd count: a copy follows the last).
 inline long long line_launches(const LinePlan& p, int nsteps) {
   long long n = nsteps / p.steps + (nsteps % p.steps != 0);
-  if (p.halo > 0) n += n & 1;
+  if (p.halo > 0 && n % 2 == 1 && n < nsteps) ++n;
   return n;
 }
 inline int line_launch_steps(int nsteps, long long launches, long long k) {

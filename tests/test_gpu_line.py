@@ -52,3 +52,21 @@ def test_line_runs_equal_stage_launches(n, order, kind, p, mode):
         out.append(U)
     assert torch.isfinite(out[1]).all()
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("order", [3, 4])
+@pytest.mark.parametrize("kind", ["sod", "sod_periodic"])
+def test_odd_runs_of_one_step_per_launch(order, kind):
+    """900001 cells of the Euler system at P4: the plan takes one step per launch (on 256 compute units), so three steps
+    end in the second array and are copied back."""
+    from paper_2309_12019_amd import dgweno
+    w = _problem(kind, 900001, 4, order, 2)
+    g = dgweno.DG.from_workload(w)
+    U0 = g.initial_state(w)
+    out = []
+    for fused in (-1, 0):
+        g.set_fused(fused)
+        out.append(g.run(U0.clone(), w.dt(), 3))
+    torch.cuda.synchronize()
+    assert torch.isfinite(out[1]).all() and not torch.equal(out[1], U0)
+    assert torch.equal(out[0], out[1])
