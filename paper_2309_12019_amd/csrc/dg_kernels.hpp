@@ -747,19 +747,18 @@ struct Cell {
   // for sensor(); the arithmetic is the same either way.  The three parts
   // (gamma_of, residual, finish) may also run on different threads.
   // XBC: compile the BC_RIEMANN exterior state in (the per-stage kernel only).
-  // gam_out, where given, receives gamma_e, before the residual: a branch
-  // after the arithmetic lets the compiler sink the arithmetic behind it, past
-  // the LDS reads that it needs.  (The kernels with the general sensor, whose
-  // branches do that anyway, keep the store at the end: 1 % faster there.)
-  template <bool SB = true, bool XBC = false>
+  // gam_out, where given, receives gamma_e, with EARLY before the residual: a
+  // branch after the arithmetic lets the compiler sink the arithmetic behind
+  // it, past the LDS reads that it needs (stage_settles).
+  template <bool SB = true, bool XBC = false, bool EARLY = false>
   __device__ static inline void rhs(const StageArgs& A, const double* b, const double (&c)[NL], int ix, int iy,
                                     double (&L)[NL], double* gam_out = nullptr) {
     const double gam = gamma_of<SB>(A, b, c, ix, iy);
-    if (MODE != MODE_WENO && gam_out) *gam_out = gam;
+    if (EARLY && gam_out) *gam_out = gam;
     double R[NL], lam;
     residual<XBC>(A, b, c, ix, iy, R, lam);
     finish(A, c, gam, lam, R, L);
-    if (MODE == MODE_WENO && gam_out) *gam_out = gam;
+    if (!EARLY && gam_out) *gam_out = gam;
   }
 
   // The moments of face f of the cell (0: -x, 1: +x, 2: -y, 3: +y), oriented
@@ -1269,6 +1268,33 @@ __device__ inline void store_second(const StageArgs& A, size_t cell, const doubl
   for (int j = 0; j < NL; ++j) A.out2[cell * NL + j] = fma(A.a2, un[j], A.b2 * fma(A.dt2, L[j], c[j]));
 }
 
+// Whether a stage kernel settles its L (and gamma_e before it), so that the
+// arithmetic ends before the branch that loads U^n.  That takes a quarter of
+// the registers of the kernels below; the others run from 2 to 10 % faster
+// with the arithmetic sunk behind that branch, where it hides the loads.
+//   * the paper's exponents: every kernel;
+//   * 2D without that sensor: P4 (LO / Zhao, us per RK3 step, unsettled ->
+//     settled: 512^2 rotation 114 -> 106 / 148 -> 126, Burgers 130 -> 121 /
+//     163 -> 143; see kUnsettledCells), P3 on single meshes (Zhao 400^2 71.3 ->
+//     60.2), and the KPP flux in batches (24 x 64^2 LO P3 226 -> 146, P4 323 ->
+//     194).  Not batches at P3 (LO, 4 x 48^2 22.8 -> 24.2, 24 x 64^2 37.8 ->
+//     41.4), P1 and P2 (1 to 4 %) and 1D (batch of 4 x 960 cells, LO P2 10.6
+//     -> 11.2).
+template <int DIM, int P, int FLUX, int MODE>
+__host__ __device__ constexpr bool stage_settles(bool batch) {
+  if (MODE == MODE_WENO1) return true;
+  if (MODE == MODE_WENO || DIM == 1) return false;
+  return FLUX == FLUX_KPP ? batch : P == 4 || (P == 3 && !batch);
+}
+
+// P4 of the modes without a sensor beyond this many cells (three states of
+// 200 B a cell are then larger than the 256 MB last-level cache, and the
+// latency that the settled kernel leaves in the open is the memory's): the
+// unsettled kernel.  LO, us per step, settled -> unsettled: 640^2 rotation 157
+// -> 162, Burgers 176 -> 184; 800^2 296 -> 278, 300 -> 300; 1024^2 513 -> 458,
+// 517 -> 486.
+constexpr long long kUnsettledCells = 256ll * 1024 * 1024 / (3 * 25 * 8);
+
 // One tile of the fused stage: TX*TY threads, one per cell.  Each thread
 // loads its own cell's coefficients into registers (a wave covers a
 // contiguous span of the cell-major state) and publishes them in the
@@ -1280,8 +1306,8 @@ __device__ inline void store_second(const StageArgs& A, size_t cell, const doubl
 // barrier); the cells then add their faces' moments in the order of the
 // per-cell evaluation, so the result is the same bit for bit.
 // XBC: compile the BC_RIEMANN exterior state in (2D Burgers per-stage kernel).
-// SECOND: compile the second combination in.
-template <int DIM, int P, int FLUX, int MODE, int TX, int TY, bool XBC = false, bool SECOND = false>
+// SECOND: compile the second combination in.  SETTLE: see stage_settles.
+template <int DIM, int P, int FLUX, int MODE, int TX, int TY, bool XBC, bool SECOND, bool SETTLE>
 __device__ inline void stage_tile(const StageArgs& A, double* lds, int ix0, int iy0) {
   using G = TileGeom<DIM, TX, TY>;
   using C = Cell<DIM, P, FLUX, MODE, G::S, G::W>;
@@ -1363,7 +1389,7 @@ __device__ inline void stage_tile(const StageArgs& A, double* lds, int ix0, int 
     double* const gam_out = A.gamma ? A.gamma + cell : nullptr;
     if constexpr (SHARE) {
       const double gam = C::template gamma_of<true>(A, lds + sc, c, gx, gy);
-      if (gam_out) *gam_out = gam;
+      if (SETTLE && gam_out) *gam_out = gam;
       double R[NL], lam;
       C::template residual<false, false>(A, lds + sc, c, gx, gy, R, lam);
       const int lx = t % TX, ly = t / TX;
@@ -1377,10 +1403,11 @@ __device__ inline void stage_tile(const StageArgs& A, double* lds, int ix0, int 
         C::add_face(f, g, R);
       }
       C::finish(A, c, gam, lam, R, L);
+      if (!SETTLE && gam_out) *gam_out = gam;
     } else {
-      C::template rhs<true, XBC>(A, lds + sc, c, gx, gy, L, gam_out);
+      C::template rhs<true, XBC, SETTLE>(A, lds + sc, c, gx, gy, L, gam_out);
     }
-    if constexpr (MODE != MODE_WENO) settle(L);
+    if constexpr (SETTLE) settle(L);
     double* dst = A.out + cell * NL;
     if (A.rhs_only) {
 #pragma unroll
@@ -1415,13 +1442,14 @@ __host__ __device__ constexpr int stage_min_waves(int dim, int p, int mode) {
 // checks cost every cell ~4 % of its instructions).  SECOND: the second
 // combination compiled in (launched where there is one: its code costs P2
 // kernels up to 20 VGPRs).
-template <int DIM, int P, int FLUX, int MODE, int TX, int TY, bool XBC = false, bool SECOND = false>
+template <int DIM, int P, int FLUX, int MODE, int TX, int TY, bool XBC = false, bool SECOND = false,
+          bool SETTLE = stage_settles<DIM, P, FLUX, MODE>(false)>
 __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX, stage_min_waves(DIM, P, MODE)) stage_kernel(const StageArgs A) {
   extern __shared__ double lds[];
   const int tile = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
   const int bx = tile % gridDim.x, by = tile / gridDim.x;
-  stage_tile<DIM, P, FLUX, MODE, TX, TY, XBC && DIM == 2 && FLUX == FLUX_BURGERS, SECOND>(A, lds, bx * TX,
-                                                                                        DIM == 2 ? by * TY : 0);
+  stage_tile<DIM, P, FLUX, MODE, TX, TY, XBC && DIM == 2 && FLUX == FLUX_BURGERS, SECOND, SETTLE>(
+      A, lds, bx * TX, DIM == 2 ? by * TY : 0);
 }
 
 // Small meshes on 8 x 8 tiles (the linear and Burgers fluxes): four waves
@@ -2065,7 +2093,8 @@ __device__ inline void batch_tile(const BatchStageArgs& B, double* lds, int k) {
   A.a = B.a;
   A.b = B.b;
   A.rhs_only = 0;
-  stage_tile<DIM, P, FLUX, MODE, TX, TY>(A, lds, tl.ix0, tl.iy0);
+  stage_tile<DIM, P, FLUX, MODE, TX, TY, false, false, stage_settles<DIM, P, FLUX, MODE>(true)>(A, lds, tl.ix0,
+                                                                                              tl.iy0);
 }
 
 // ONE: one workgroup per tile (grid = the number of tiles), no tile loop;

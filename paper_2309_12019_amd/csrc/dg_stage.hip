@@ -24,14 +24,18 @@ constexpr int mode16() {
   return MODE == MODE_WENO1 && (DGK_P == 1 || (DGK_P == 2 && FLUX == FLUX_LINADV)) ? (int)MODE_WENO : MODE;
 }
 
-template <int FLUX, int MODE0, int TX, int TY, bool XBC = false, bool SECOND = false>
+template <int FLUX, int MODE0, int TX, int TY, bool XBC = false, bool SECOND = false, bool LARGE = false>
 hipError_t launch_tile(const StageArgs& A, hipStream_t st) {
   constexpr int NL = DGK_DIM == 1 ? DGK_P + 1 : (DGK_P + 1) * (DGK_P + 1);
   constexpr int MODE = DGK_DIM == 2 && TX == 16 ? mode16<FLUX, MODE0>() : MODE0;
   if constexpr (DGK_DIM == 2 && !SECOND) {
     if (A.out2) return launch_tile<FLUX, MODE0, TX, TY, XBC, true>(A, st);
   }
-  auto k = stage_kernel<DGK_DIM, DGK_P, FLUX, MODE, TX, TY, XBC, SECOND>;
+  if constexpr (DGK_DIM == 2 && DGK_P == 4 && MODE0 <= MODE_LO && FLUX != FLUX_KPP && !LARGE) {
+    if ((long long)A.nx * A.ny > kUnsettledCells) return launch_tile<FLUX, MODE0, TX, TY, XBC, SECOND, true>(A, st);
+  }
+  constexpr bool SETTLE = !LARGE && stage_settles<DGK_DIM, DGK_P, FLUX, MODE>(false);
+  auto k = stage_kernel<DGK_DIM, DGK_P, FLUX, MODE, TX, TY, XBC, SECOND, SETTLE>;
   const size_t lds = sizeof(double) * (size_t)stage_lds_doubles(DGK_DIM, NL, FLUX, TX, TY);
   if (lds > 65536) {
     // tiles above 64 KB of LDS: raise the per-kernel limit to what this launch needs

@@ -1,0 +1,42 @@
+"""Batch classes and single problems whose kernels differ by the problem's
+exponents, mode and size: every problem must still advance bit for bit as it
+does alone."""
+import pytest
+import torch
+
+from paper_2309_12019_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _run_both(ws, steps=3):
+    """(states of a batch run, states of single runs on per-stage launches)"""
+    from paper_2309_12019_amd import dgweno
+    B = dgweno.Batch.from_workloads(ws)
+    arena = B.empty()
+    alone = []
+    for w, v in zip(ws, B.views(arena)):
+        g = dgweno.DG.from_workload(w)
+        g.set_fused(0)
+        v.copy_(g.initial_state(w))
+        alone.append(g.run(v.clone(), w.dt(), steps))
+    B.run(arena, [w.dt() for w in ws], steps)
+    torch.cuda.synchronize()
+    return B, B.views(arena), alone
+
+
+def _check(ws, steps=3):
+    B, batch, alone = _run_both(ws, steps)
+    for w, a, b in zip(ws, batch, alone):
+        assert torch.isfinite(b).all()
+        assert torch.equal(a, b), (w.name, w.nx, w.p, w.mode, w.q, w.r)
+    return B
+
+
+@pytest.mark.parametrize("p,cells", [(4, 669), (4, 668), (3, 90)])
+@pytest.mark.parametrize("kind", ["rot", "burgers"])
+def test_modes_without_a_sensor_at_the_edge_of_the_large_kernel(kind, p, cells):
+    """P4 single problems beyond kUnsettledCells (447392 cells: 669 x 669 and not 669 x 668) take another instantiation
+    than batches do; P3 single problems another than P3 batches at any size."""
+    make = inputs.rot2d if kind == "rot" else inputs.burgers2d
+    _check([make(669 if p == 4 else cells, p, seed=2, ny=cells, mode=inputs.MODE_LO, steps=1)], steps=2)
