@@ -2065,7 +2065,10 @@ struct BatchStageArgs {
 // A struct of the tables above, which no kernel writes, from an address that
 // is the same for the whole workgroup: through the constant address space,
 // so that its fields are scalar loads into SGPRs.  As ordinary loads they
-// come through the vector cache into some 80 VGPRs.
+// come through the vector cache into some 80 VGPRs, which only the 2D kernels
+// with the general sensor have left: those wait for the scalar loads instead
+// (8 problems of 300^2 P2 rotation 101.5 -> 104.6 us per step, 24 of 64^2 P4
+// KPP 352 -> 357), and keep the ordinary ones.
 template <class T>
 __device__ inline T load_uniform(const T* p) {
   static_assert(sizeof(T) % 8 == 0 && alignof(T) <= 8, "copied in words of 8 bytes");
@@ -2082,7 +2085,11 @@ __device__ inline T load_uniform(const T* p) {
 template <int DIM, int P, int FLUX, int MODE, int TX, int TY>
 __device__ inline void batch_tile(const BatchStageArgs& B, double* lds, int k) {
   const BatchTile tl = load_uniform(B.tiles + k);
-  const BatchProblem pr = load_uniform(B.probs + tl.prob);
+  BatchProblem pr;
+  if constexpr (DIM == 1 || MODE != MODE_WENO)
+    pr = load_uniform(B.probs + tl.prob);
+  else
+    pr = B.probs[tl.prob];
   StageArgs A = pr.args;
   const long long off = pr.off;
   A.uin = B.uin + off;

@@ -40,3 +40,22 @@ def test_modes_without_a_sensor_at_the_edge_of_the_large_kernel(kind, p, cells):
     than batches do; P3 single problems another than P3 batches at any size."""
     make = inputs.rot2d if kind == "rot" else inputs.burgers2d
     _check([make(669 if p == 4 else cells, p, seed=2, ny=cells, mode=inputs.MODE_LO, steps=1)], steps=2)
+
+
+@pytest.mark.parametrize("p", [1, 2, 3, 4])
+@pytest.mark.parametrize("kind", ["adv1d", "burgers1d", "rot2d", "burgers2d", "kpp2d"])
+def test_a_class_of_mixed_exponents(kind, p):
+    """A class holds every problem of its mode: with exponents other than the paper's in one of them, all of it takes the
+    general sensor's kernels (single problems take their own)."""
+    ws = []
+    for i, (q, r) in enumerate([(1.0, 2.0), (2.0, 2.0), (1.0, 3.0), (1.0, 2.0)]):
+        n = 17 + 6 * i
+        w = {"adv1d": lambda: inputs.adv1d(9 * n, p), "burgers1d": lambda: inputs.burgers1d(9 * n, p),
+             "rot2d": lambda: inputs.rot2d(n, p, seed=i, ny=n - 4),
+             "burgers2d": lambda: inputs.burgers2d(n, p, seed=i, ny=n + 3, steps=1),
+             "kpp2d": lambda: inputs.kpp2d(n, p, steps=1)}[kind]()
+        w.q, w.r = q, r
+        ws.append(w)
+    for some in (ws, ws[1:3], ws[:1] + ws[3:]):   # mixed; general only; the paper's only
+        B = _check(some)
+        assert B.num_classes() == 1 and B.schedule(0)["problems"] == len(some)
