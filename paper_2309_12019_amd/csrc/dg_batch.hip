@@ -259,8 +259,16 @@ int dg_batch_create(const dg_mesh_desc* descs, int32_t count, dg_batch** out) {
     c.tx = d.dim == 1 ? 256 : 16;
     c.ty = d.dim == 1 ? 1 : 16;
     // P4: one-wave tiles, as for single problems (128 mixed problems 740 -> 719
-    // us per step, 24 problems 276 -> 260, 400 problems 1027 -> 1008; P3 level)
-    if (lds_bytes(c.dim, c.nl, c.flux, c.tx, c.ty) > (size_t)b->max_lds || (c.dim == 2 && c.p == 4)) c.tx = c.ty = 8;
+    // us per step, 24 problems 276 -> 260, 400 problems 1027 -> 1008; P3 level),
+    // but not the KPP flux with general exponents past four of them per compute
+    // unit (4 problems of 48^2 168 -> 157, but 24 of 64^2 344 -> 357 and 48 of
+    // 64^2 521 -> 547)
+    long long t8 = 0;
+    for (int i : probs)
+      if (d.dim == 2) t8 += (long long)((b->d[i].nx + 7) / 8) * ((b->d[i].ny + 7) / 8);
+    const bool kpp16 = d.flux == DG_FLUX_KPP && c.kmode == dgk::MODE_WENO && t8 > 4LL * b->cus;
+    if (lds_bytes(c.dim, c.nl, c.flux, c.tx, c.ty) > (size_t)b->max_lds || (c.dim == 2 && c.p == 4 && !kpp16))
+      c.tx = c.ty = 8;
     c.probs = probs;
     c.cap = dgk::batch_tile_capacity(b->mesh, probs);
     b->cls.push_back(c);

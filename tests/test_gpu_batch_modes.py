@@ -59,3 +59,13 @@ def test_a_class_of_mixed_exponents(kind, p):
     for some in (ws, ws[1:3], ws[:1] + ws[3:]):   # mixed; general only; the paper's only
         B = _check(some)
         assert B.num_classes() == 1 and B.schedule(0)["problems"] == len(some)
+
+
+@pytest.mark.parametrize("n,tile,q", [(256, 8, 2.0), (264, 16, 2.0), (264, 8, 1.0)])
+def test_kpp_p4_batches_take_16x16_tiles_past_four_small_ones_per_compute_unit(n, tile, q):
+    """With general exponents (the tile stated is for 256 compute units: 1024 tiles of 8x8 cells, and 1089)."""
+    w = inputs.kpp2d(n, 4, steps=1)
+    w.q = q
+    B = _check([w], steps=1)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert (B.schedule(0)["tx"], B.schedule(0)["ty"]) == (tile, tile)
