@@ -22,8 +22,7 @@ constexpr double kEulerGamma = 1.4;
 
 // n / d from r = rcp(d): the quotient and one correction by its exact
 // residual, as the division instruction sequence does, without that sequence's
-// scaling of the operands (which only denormal and near-overflow values need);
-// r serves every quotient with the same denominator
+// scaling of the operands; r serves every quotient with the same denominator
 __device__ inline double div_by(double n, double d, double r) {
   const double q = n * r;
   return fma(fma(-d, q, n), r, q);
@@ -31,34 +30,58 @@ __device__ inline double div_by(double n, double d, double r) {
 
 // sqrt(x): hardware estimate and two corrections by the exact residual (after
 // the first up to 1.5 units in the last place are left, after the second the
-// rounding); 0 and infinity pass through (their correction is 0 * inf),
-// negative x gives NaN
+// rounding), without scaling
 __device__ inline double sqrt_corr(double x) {
   const double s = __builtin_amdgcn_sqrt(x), h = 0.5 * rcp(s);
   const double s1 = fma(h, fma(-s, s, x), s);
-  const double y = fma(h, fma(-s1, s1, x), s1);
-  return s == 0.0 || s == __builtin_inf() ? s : y;
+  return fma(h, fma(-s1, s1, x), s1);
+}
+
+// kRangeWidth or more unless x lies in [2^-300, 2^300)
+constexpr uint32_t kRangeWidth = 600u << 20;
+__device__ inline uint32_t off_range(double x) {
+  return (uint32_t)((uint64_t)__double_as_longlong(x) >> 32) - ((1023u - 300u) << 20);
 }
 
 // F(u) and |v| + c of one state.  Eight of these per cell and operator
-// evaluation are most of the Euler kernels' arithmetic: two divisions by the
-// density share its reciprocal, and neither they nor the square root scale
-// their operands (DIVSQRT instructions per state instead of DIVSQRT0)
-__device__ inline void euler_flux(const double (&u)[3], double (&F)[3], double& speed) {
-  const double r = rcp(u[0]);
-  const double v = div_by(u[1], u[0], r);
-  const double p = (kEulerGamma - 1.0) * (u[2] - 0.5 * u[1] * v);
+// evaluation are most of the Euler kernels' arithmetic, so two divisions by
+// the density share its reciprocal and neither they nor the square root scale
+// their operands (Sod P2, per step: 128 cells 4.9 -> 4.2 us, 2^20 cells 78 ->
+// 67).  They give what / and sqrt give, rounded alike, except that a quotient
+// whose numerator is below 2^-970 may be off by a unit in the last place, as
+// long as p / rho lies in the middle range.  Where it does not (a vacuum, an
+// infinite or NaN component, an overflow on the way: all of them end there, or
+// in a p / rho that is not a number) `off` is raised to kRangeWidth or more,
+// and the caller takes the cell again with EXACT, on / and sqrt.
+template <bool EXACT>
+__device__ inline void euler_flux(const double (&u)[3], double (&F)[3], double& speed, uint32_t& off) {
+  double v, p, c;
+  if constexpr (EXACT) {
+    v = u[1] / u[0];
+    p = (kEulerGamma - 1.0) * (u[2] - 0.5 * u[1] * v);
+    c = sqrt(kEulerGamma * p / u[0]);
+  } else {
+    const double r = rcp(u[0]);
+    v = div_by(u[1], u[0], r);
+    p = (kEulerGamma - 1.0) * (u[2] - 0.5 * u[1] * v);
+    const double x = div_by(kEulerGamma * p, u[0], r);
+    c = sqrt_corr(x);
+    off = max(off, off_range(x));
+  }
   F[0] = u[1];
   F[1] = fma(u[1], v, p);
   F[2] = (u[2] + p) * v;
-  speed = fabs(v) + sqrt_corr(div_by(kEulerGamma * p, u[0], r));
+  speed = fabs(v) + c;
 }
 
 // H . n of the LLF flux for the outward normal n = side
-__device__ inline void llf_euler(double side, const double (&um)[3], const double (&up)[3], double (&H)[3]) {
+template <bool EXACT>
+__device__ inline void llf_euler(double side, const double (&um)[3], const double (&up)[3], double (&H)[3],
+                                 uint32_t& off) {
   double Fm[3], Fp[3], sm, sp;
-  euler_flux(um, Fm, sm);
-  euler_flux(up, Fp, sp);
+  euler_flux<EXACT>(um, Fm, sm, off);
+  if constexpr (EXACT) __builtin_amdgcn_sched_barrier(0);
+  euler_flux<EXACT>(up, Fp, sp, off);
   const double s = fmax(sm, sp);
 #pragma unroll
   for (int k = 0; k < 3; ++k) H[k] = 0.5 * side * (Fm[k] + Fp[k]) - 0.5 * s * (up[k] - um[k]);
@@ -75,7 +98,8 @@ struct EulerCell {
 
   // Volume terms int phi_a' F(u_h) of the three components (R[k][0] = 0) and
   // lambda_e, from the cell's coefficients c[k][a]
-  __device__ static inline void volume(const double (&c)[3][N], double (&R)[3][N], double& lam) {
+  template <bool EXACT>
+  __device__ static inline void volume(const double (&c)[3][N], double (&R)[3][N], double& lam, uint32_t& off) {
 #pragma unroll
     for (int k = 0; k < 3; ++k)
 #pragma unroll
@@ -92,7 +116,7 @@ struct EulerCell {
         u[k] = t;
       }
       double F[3], sp;
-      euler_flux(u, F, sp);
+      euler_flux<EXACT>(u, F, sp, off);
       lam = fmax(lam, sp);
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
@@ -100,13 +124,15 @@ struct EulerCell {
 #pragma unroll
         for (int a = 1; a < N; ++a) R[k][a] = fma(TB::nd.D[a][q], wF, R[k][a]);
       }
+      if constexpr (EXACT) __builtin_amdgcn_sched_barrier(0);
     }
   }
 
   // LLF flux through face f (0: x_{e-1/2}, 1: x_{e+1/2}) along its outward
   // normal.  b: the cell's slot in the LDS tile (plane j = k N + a).
+  template <bool EXACT>
   __device__ static inline void face_flux(const StageArgs& A, const double* b, const double (&c)[3][N], int ix, int f,
-                                          double (&H)[3]) {
+                                          double (&H)[3], uint32_t& off) {
     const bool wall = !A.per_x && (f ? ix == A.nx - 1 : ix == 0);
     double um[3], up[3];
 #pragma unroll
@@ -127,7 +153,7 @@ struct EulerCell {
       up[1] = -um[1];
       up[2] = um[2];
     }
-    llf_euler(f ? 1.0 : -1.0, um, up, H);
+    llf_euler<EXACT>(f ? 1.0 : -1.0, um, up, H, off);
   }
 
   // - phi_a H . n of face f into R
@@ -138,15 +164,38 @@ struct EulerCell {
       for (int a = 0; a < N; ++a) R[k][a] = fma(f ? -1.0 : -TB::dg.sgn[a], H[k], R[k][a]);
   }
 
+  // Makes the cell's coefficients and slot (returned) values that the compiler
+  // does not know to be the ones it had: a second, EXACT evaluation from them
+  // then shares nothing with the first, whose node and face states would stay
+  // live (P2: 80 VGPRs)
+  __device__ static inline const double* again(const double* b, double (&c)[3][N]) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) settle(c[k]);
+    int z = 0;
+    asm volatile("" : "+v"(z));
+    return b + z;
+  }
+
   // Volume minus face terms for the three components, and lambda_e
-  __device__ static inline void residual(const StageArgs& A, const double* b, const double (&c)[3][N], int ix,
-                                         double (&R)[3][N], double& lam) {
-    volume(c, R, lam);
+  template <bool EXACT>
+  __device__ static inline void residual_pass(const StageArgs& A, const double* b, const double (&c)[3][N], int ix,
+                                              double (&R)[3][N], double& lam, uint32_t& off) {
+    volume<EXACT>(c, R, lam, off);
 #pragma unroll
     for (int f = 0; f < 2; ++f) {
       double H[3];
-      face_flux(A, b, c, ix, f, H);
+      if constexpr (EXACT) __builtin_amdgcn_sched_barrier(0);
+      face_flux<EXACT>(A, b, c, ix, f, H, off);
       add_face(f, H, R);
+    }
+  }
+  __device__ static inline void residual(const StageArgs& A, const double* b, double (&c)[3][N], int ix,
+                                         double (&R)[3][N], double& lam) {
+    uint32_t off = 0;
+    residual_pass<false>(A, b, c, ix, R, lam, off);
+    if (__builtin_expect(off >= kRangeWidth, 0)) {
+      b = again(b, c);
+      residual_pass<true>(A, b, c, ix, R, lam, off);
     }
   }
 };
@@ -337,12 +386,13 @@ __global__ void __launch_bounds__(256) euler_lambda_kernel(const StageArgs A, co
       const double* c = U + e * 3 * N;
       for (int q = 0; q < Q; ++q) {
         double u[3], F[3], sp;
+        uint32_t off = 0;
         for (int k = 0; k < 3; ++k) {
           double s = 0.0;
           for (int a = 0; a < N; ++a) s = fma(c[k * N + a], TB::nd.L[a][q], s);
           u[k] = s;
         }
-        euler_flux(u, F, sp);
+        euler_flux<true>(u, F, sp, off);
         lam = fmax(lam, sp);
       }
     }

@@ -201,15 +201,23 @@ __global__ void __launch_bounds__(SPLIT ? kLineSplitThreads : kLineThreads) line
   // cell t at slot t + 1; on a periodic mesh of one workgroup each end cell
   // also fills the slot beyond the other end
   const bool ring = B.halo == 0 && A.per_x;
-  // otherwise the slots beyond the workgroup's cells hold the exterior state
-  // (only stale cells and the ends of a non-periodic mesh read them)
-  if (owner && t < 2 && !ring) {
-    const int end = t == 0 ? 0 : (B.own + 2 * B.halo) + 1;
+  // otherwise the slots beyond the workgroup's cells, which only stale cells
+  // and the ends of a non-periodic mesh read, hold the exterior state; in the
+  // windows of an Euler mesh the end cells' first, so that stale cells are
+  // states of a gas (off the middle range their evaluations would be repeated,
+  // euler_flux)
+  const int last = B.own + 2 * B.halo - 1;
+  const bool echo = FLUX == FLUX_EULER && B.halo > 0;
 #pragma unroll
-    for (int k = 0; k < 2; ++k)
+  for (int e = 0; e < 2; ++e)
+    if (owner && !ring && t == (e ? last : 0)) {
 #pragma unroll
-      for (int j = 0; j < NV; ++j) lds[(k * NV + j) * S + end] = j == 0 ? A.bc : 0.0;
-  }
+      for (int j = 0; j < NV; ++j) {
+        const double v = echo ? c[j] : (j == 0 ? A.bc : 0.0);
+        lds[j * S + (e ? last + 2 : 0)] = v;
+        lds[(NV + j) * S + (e ? last + 2 : 0)] = v;
+      }
+    }
   int par = 0;
   // L := L(c); the state is published in this evaluation's buffer first
   auto eval = [&](double (&L)[NV]) {
@@ -220,9 +228,9 @@ __global__ void __launch_bounds__(SPLIT ? kLineSplitThreads : kLineThreads) line
       for (int j = 0; j < NV; ++j) buf[j * S + t + 1] = c[j];
       if (ring && t == 0) {
 #pragma unroll
-        for (int j = 0; j < NV; ++j) buf[j * S + B.own + 1] = c[j];
+        for (int j = 0; j < NV; ++j) buf[j * S + last + 2] = c[j];
       }
-      if (ring && t == B.own - 1) {
+      if (ring && t == last) {
 #pragma unroll
         for (int j = 0; j < NV; ++j) buf[j * S] = c[j];
       }
@@ -238,7 +246,12 @@ __global__ void __launch_bounds__(SPLIT ? kLineSplitThreads : kLineThreads) line
         for (int j = 0; j < NV; ++j) u[j / N][j % N] = owner ? c[j] : buf[j * S + t + 1];
         if (role == 0) {
           double R[3][N], lam;
-          E::volume(u, R, lam);
+          uint32_t off = 0;
+          E::template volume<false>(u, R, lam, off);
+          if (__builtin_expect(off >= kRangeWidth, 0)) {
+            E::again(buf, u);
+            E::template volume<true>(u, R, lam, off);
+          }
 #pragma unroll
           for (int j = 0; j < NV; ++j)
             if (j % N) ex[j * S] = R[j / N][j % N];
@@ -246,8 +259,14 @@ __global__ void __launch_bounds__(SPLIT ? kLineSplitThreads : kLineThreads) line
         } else if (role == 2) {
           ex[(NV + 1) * S] = LC::C::template gamma_of<true>(A, buf + t + 1, u[0], wx, 0);
         } else {
+          uint32_t off = 0;
 #pragma unroll
-          for (int f = 0; f < 2; ++f) E::face_flux(A, buf + t + 1, u, wx, f, H[f]);
+          for (int f = 0; f < 2; ++f) E::template face_flux<false>(A, buf + t + 1, u, wx, f, H[f], off);
+          if (__builtin_expect(off >= kRangeWidth, 0)) {
+            const double* const bx = E::again(buf + t + 1, u);
+#pragma unroll
+            for (int f = 0; f < 2; ++f) E::template face_flux<true>(A, bx, u, wx, f, H[f], off);
+          }
         }
       }
       tile_barrier();
