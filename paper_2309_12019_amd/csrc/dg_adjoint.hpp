@@ -319,8 +319,13 @@ struct AdjCell {
     for (int f = 0; f < NF; ++f) {
       C::template cand_any<0>(f, b, cd);
       beta[f + 1] = C::qform(cd);
-      const double wl = A.wnb * C::weight(A, beta[f + 1]);
-      al[f + 1] = has[f] ? wl : 0.0;
+      if constexpr (MODE == MODE_WENO1) {
+        const double wl = A.wnb * C::weight(A, beta[f + 1]);  // (first, so that the choice is a select)
+        al[f + 1] = has[f] ? wl : 0.0;
+      } else {
+        // (as a select it costs 16 VGPRs at P1 and P2: three waves per SIMD instead of four)
+        al[f + 1] = has[f] ? A.wnb * C::weight(A, beta[f + 1]) : 0.0;
+      }
       m += has[f];
       if constexpr (SB) __builtin_amdgcn_sched_barrier(0);
     }
