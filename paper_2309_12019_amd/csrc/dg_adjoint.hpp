@@ -452,10 +452,14 @@ struct AdjCell {
     constexpr int axis = F >> 1;
     constexpr bool plus = F & 1;
     const double s = plus ? 1.0 : -1.0;
+    // sums that start with their first product; from P3 on with a cleared
+    // accumulator, which the linear flux's shared launch at P3 needs to keep two
+    // waves per SIMD (255 VGPRs against 256 and 5 AGPRs)
+    constexpr bool FIRST = P <= 2;
     double tm[N], tp[N], sm[N], sp[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-      double t, tn, gt, gn;
+      double t = 0.0, tn = 0.0, gt = 0.0, gn = 0.0;
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         const int j = axis == 0 ? i + N * k : k + N * i;
@@ -464,17 +468,17 @@ struct AdjCell {
         const double cn = b[j * S + C::off(F)];
         const double gf = sn * (P <= 2 ? A.lfac[i + N * k] : g2h * TB::dg.minv[i] * TB::dg.minv[k]);
         const double vn = bv[j * S + C::off(F)];
-        t = i == 0 ? c[j] : fma(so, c[j], t);
-        tn = i == 0 ? cn : fma(sn, cn, tn);
-        gt = i == 0 ? g[j] : fma(so, g[j], gt);
-        gn = i == 0 ? gf * vn : fma(gf, vn, gn);
+        t = i == 0 && FIRST ? c[j] : fma(so, c[j], t);
+        tn = i == 0 && FIRST ? cn : fma(sn, cn, tn);
+        gt = i == 0 && FIRST ? g[j] : fma(so, g[j], gt);
+        gn = i == 0 && FIRST ? gf * vn : fma(gf, vn, gn);
       }
       tm[k] = t;
       tp[k] = tn;
       sm[k] = gt;
       sp[k] = gn;
     }
-    double acc[N];
+    double acc[N] = {};
 #pragma unroll
     for (int r = 0; r < Q; ++r) {
       double um = tm[0], up = tp[0], gm = sm[0], gp = sp[0];
@@ -488,7 +492,7 @@ struct AdjCell {
       const double vax = axis == 0 ? vxl[r] : vyl[r];
       const double dl = TB::nd.w[r] * (gm - gp) * dllf(s, vax, um, up);
 #pragma unroll
-      for (int k = 0; k < N; ++k) acc[k] = r == 0 ? TB::nd.L[k][r] * dl : fma(TB::nd.L[k][r], dl, acc[k]);
+      for (int k = 0; k < N; ++k) acc[k] = r == 0 && FIRST ? TB::nd.L[k][r] * dl : fma(TB::nd.L[k][r], dl, acc[k]);
     }
 #pragma unroll
     for (int k = 0; k < N; ++k)

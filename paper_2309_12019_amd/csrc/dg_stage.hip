@@ -222,13 +222,18 @@ hipError_t launch_adj_tile(const LaunchReq* r) {
   dim3 block(DGK_DIM == 2 ? TX * TY : TX);
   const bool sens = r->kind == LAUNCH_ADJ_SENSOR;
   const size_t lds = sizeof(double) * (size_t)NL * S * (sens ? 1 : 2);
+  // the shared launch of the linear flux at P3 keeps the sensor's branches: two
+  // waves per SIMD, one without them (255 VGPRs against 256 and 6 AGPRs; rotation,
+  // us per step of a whole gradient, 48^2 112 -> 99, 400^2 342 -> 319)
+  constexpr int GSMODE =
+      MODE == MODE_WENO1 && DGK_DIM == 2 && DGK_P == 3 && FLUX == FLUX_LINADV ? (int)MODE_WENO : MODE;
   const void* k;
   if (r->kind == LAUNCH_ADJ_GRAD_SENSOR) {
     // only the stabilised operator has a sensor to reverse
     if constexpr (!is_weno(MODE))
       return hipErrorInvalidValue;
     else
-      k = reinterpret_cast<const void*>(adj_grad_sensor_kernel<DGK_DIM, DGK_P, FLUX, MODE, TX, TY>);
+      k = reinterpret_cast<const void*>(adj_grad_sensor_kernel<DGK_DIM, DGK_P, FLUX, GSMODE, TX, TY>);
   } else {
     k = sens ? reinterpret_cast<const void*>(adj_sensor_kernel<DGK_DIM, DGK_P, FLUX, MODE, TX, TY>)
              : reinterpret_cast<const void*>(adj_grad_kernel<DGK_DIM, DGK_P, FLUX, MODE, TX, TY>);
@@ -239,7 +244,7 @@ hipError_t launch_adj_tile(const LaunchReq* r) {
   }
   if (r->kind == LAUNCH_ADJ_GRAD_SENSOR) {
     if constexpr (is_weno(MODE))
-      hipLaunchKernelGGL((adj_grad_sensor_kernel<DGK_DIM, DGK_P, FLUX, MODE, TX, TY>), grid, block, lds, r->stream,
+      hipLaunchKernelGGL((adj_grad_sensor_kernel<DGK_DIM, DGK_P, FLUX, GSMODE, TX, TY>), grid, block, lds, r->stream,
                          Ad);
   } else if (sens) {
     hipLaunchKernelGGL((adj_sensor_kernel<DGK_DIM, DGK_P, FLUX, MODE, TX, TY>), grid, block, lds, r->stream, Ad);
