@@ -512,9 +512,15 @@ long long step_tiles16(const dg_ctx* c) {
 // past one 16x16 tile per compute unit, where a run's two buffers stay in the
 // caches, a sweep that stores checkpoints between steps does not (512^2
 // Burgers: 55 us per step against 53 in three stages); 400^2 P1 gains (whole
-// gradient 686 -> 627 us).
+// gradient 686 -> 627 us).  With a general power in every weight, which the
+// step's rings recompute, stages past one tile per compute unit too (us per
+// step of a whole gradient, stages -> fused: 400^2 P1 rotation 149 -> 154, 2^19
+// cells P1 advection 201 -> 209; 256^2 94 -> 91 and 65536 cells 65 -> 63).
 int advance(dg_ctx* c, hipStream_t st, const double* src, double* dst, double dt, int steps) {
-  const bool fused = c->fused && (c->d.dim == 1 || c->d.p == 1 || step_tiles16(c) <= c->cus);
+  const long long tiles =
+      c->d.dim == 1 ? ((long long)c->d.nx + dgk::kStepTile1D - 1) / dgk::kStepTile1D : step_tiles16(c);
+  const bool power = c->d.mode == DG_MODE_WENO && c->d.weno_pow != 2.0;
+  const bool fused = c->fused && (tiles <= c->cus || ((c->d.dim == 1 || c->d.p == 1) && !power));
   for (int k = 0; k < steps; ++k) {
     double* out = fused && (steps - 1 - k) % 2 ? c->U1 : dst;
     const int rc = fused && out != src ? step_fused(c, st, src, out, dt) : rk3_step_to(c, st, src, out, dt);

@@ -33,3 +33,24 @@ def test_advance_equals_stage_launches(steps, snaps, keep, kind, p, mode):
         assert torch.equal(T.detach(), V)
         out.append(grad)
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("r", [2.0, 3.0])
+@pytest.mark.parametrize("cells", [256 * 256, 256 * 256 + 1])
+def test_general_power_past_one_tile_per_compute_unit(cells, r):
+    """1D P1 at and one cell past 256 tiles of 256 cells: with a general power in the weights the larger mesh advances in
+    stages on 256 compute units, bit for bit as the step kernel does."""
+    from paper_2309_12019_amd import dgweno
+    w = inputs.adv1d(cells, 1)
+    w.r = r
+    g = dgweno.DG.from_workload(w)
+    U0 = g.initial_state(w)
+    out = []
+    for fused in (-1, 0):
+        g.set_fused(fused)
+        U = U0.clone().requires_grad_(True)
+        T = dgweno.run_differentiable(g, U, w.dt(), 4, 1, keep_stages=False)
+        (grad,) = torch.autograd.grad(T, U, torch.ones_like(U0))
+        out.append((T.detach(), grad))
+    torch.cuda.synchronize()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
