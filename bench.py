@@ -473,7 +473,7 @@ def stage_kernel_name(w, tile):
         import torch
         cus = torch.cuda.get_device_properties(0).multi_processor_count
         t8 = ((w.nx + 7) // 8) * ((w.ny + 7) // 8)
-        if t8 <= {2: 3 if w.bc_kind == 1 else 4, 3: 2}.get(w.p, 1) * cus:
+        if t8 <= {2: 2 if w.bc_kind == 1 else 4, 3: 2}.get(w.p, 1) * cus:
             return f"roles_kernel<{w.p},{w.flux},{mode}> (8x8, four waves)"
     elif mode == 4 and (w.p == 1 or (w.p == 2 and w.flux == 0)):
         mode = 2

@@ -198,11 +198,7 @@ int stage(dg_ctx* c, hipStream_t st, const double* uin, const double* un, double
   r.args.tclock = c->tclock;
   // 8x8 tiles of several waves on meshes of a few tiles per compute unit:
   // the KPP flux by split_waves; the others four waves (roles_kernel) up to
-  // as many tiles per compute unit as its registers let share one: per stage
-  // of the rotation, four waves against one, P1 3.40 / 3.43 us at 1 and 3.56 /
-  // 3.52 at 1.27; P2 5.44 / 5.66 at 2.4 and 6.35 / 6.56 at 4; P3 6.83 / 7.69
-  // at 1.6 and 9.58 / 8.65 at 2.1; P4 7.81 / 9.50 at 1 and 13.1 / 10.4 at
-  // 1.27 (Burgers alike)
+  // roles_tiles_per_cu
   if (c->d.dim == 2 && c->tx == 8) {
     const long long t8 = (long long)((c->d.nx + 7) / 8) * ((c->d.ny + 7) / 8);
     if (c->d.flux == DG_FLUX_KPP)

@@ -1468,19 +1468,24 @@ __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX, stage_min_waves(DIM, 
 // same order as stage_tile, so the same result bit for bit.
 // XBC: the BC_RIEMANN exterior state compiled in (2D Burgers).
 constexpr int kRoleThreads = 256;
-// 8 x 8 tiles per compute unit up to which this kernel is taken.  The sensor
-// with the paper's exponents: what its registers (four waves; 60, 111, 194 and
-// 307 VGPRs) let run side by side, at P1 one, since there its second barrier
-// costs more than the split gains, and three at P2 with the exact exterior
-// state (twice the instructions).  The other modes, per ten second-order steps
-// of rotation, here against one-wave tiles: Zhao P1 150^2 99 / 105 us, P3 200^2
-// 190 / 216, P4 150^2 207 / 243, 200^2 327 / 291; LO P1 150^2 89 / 83, P2 240^2
-// 139 / 132, P3 200^2 172 / 177, P4 150^2 181 / 187, 200^2 275 / 236.
+// 8 x 8 tiles per compute unit up to which this kernel is taken (0: never):
+// as long as the tiles' registers let them share a compute unit and, without a
+// sensor to evaluate beside the rest, as far as the faces alone pay for the
+// second barrier.  Time of second-order steps here over that of one-wave
+// tiles, rotation / Burgers, at the last size taken -> at the next one timed
+// (0.8, 1, 1.3, 1.6, 1.9, 2.4, 2.9, 3.5 and 4 tiles per compute unit):
+//           DG, LO                   Zhao                     WENO
+//   P1      1.10 / 1.10 at 0.8       .99 / .99 -> 1.00/1.01   .97 / .97 -> .99/1.00
+//   P2      1.06 / 1.01 at 0.8       .94 / .92 at 4           .94 / .93 at 4
+//   P3      .95 / .92 -> .93/1.05    .88 / .84 -> .87/1.02    .88 / .84 -> 1.10/1.04
+//   P4      .95 / .90 -> 1.19/1.19   .85 / .80 -> 1.14/1.09   .82 / .78 -> 1.25/1.23
+// General exponents: P2 .99 / .93 -> 1.50/1.41 at 3, the other degrees alike;
+// P2 WENO with the exact exterior state .99 -> 1.05 at 2.
 __host__ __device__ constexpr int roles_tiles_per_cu(int p, int mode, int bc_kind) {
-  if (mode == MODE_WENO) return 3;
-  if (mode == MODE_WENO1) return p == 2 ? (bc_kind == BC_RIEMANN ? 3 : 4) : p == 3 ? 2 : 1;
-  if (p == 2) return mode == MODE_ZHAO && bc_kind != BC_RIEMANN ? 4 : 3;
-  return p == 1 ? (mode == MODE_ZHAO ? 3 : 1) : p == 3 ? 3 : 2;
+  if (mode == MODE_DG || mode == MODE_LO) return p <= 2 ? 0 : p == 3 ? 3 : 2;
+  if (p == 2 && is_weno(mode)) return bc_kind == BC_RIEMANN ? 2 : mode == MODE_WENO1 ? 4 : 3;
+  if (mode == MODE_ZHAO) return p == 1 ? 1 : p == 2 ? 4 : p == 3 ? 3 : 2;
+  return p == 3 ? 2 : 1;
 }
 __host__ __device__ inline int roles_lds_doubles(int nl, int n) {
   return tile_lds_doubles(2, nl, 8, 8) + face_lds_doubles(n, 8, 8) + 64;

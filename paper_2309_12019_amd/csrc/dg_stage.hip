@@ -105,7 +105,9 @@ hipError_t launch_stage_fm(const StageArgs& A, hipStream_t st, int waves = 0) {
     if constexpr (FLUX == FLUX_BURGERS) {
       if (A.bc_kind == BC_RIEMANN) {
         if (A.tx == 8) {
-          if (waves == 4) return launch_roles<FLUX, MODE, true>(A, st);
+          if constexpr (roles_tiles_per_cu(DGK_P, MODE, BC_RIEMANN) > 0) {
+            if (waves == 4) return launch_roles<FLUX, MODE, true>(A, st);
+          }
           return launch_tile<FLUX, MODE, 8, 8, true>(A, st);
         }
         return launch_tile<FLUX, MODE, 16, 16, true>(A, st);
@@ -115,7 +117,9 @@ hipError_t launch_stage_fm(const StageArgs& A, hipStream_t st, int waves = 0) {
       if (A.tx == 8) return launch_kpp_split<MODE>(A, st, waves);
     } else {
       if (A.tx == 8) {
-        if (waves == 4) return launch_roles<FLUX, MODE, false>(A, st);
+        if constexpr (roles_tiles_per_cu(DGK_P, MODE, BC_CONSTANT) > 0) {
+          if (waves == 4) return launch_roles<FLUX, MODE, false>(A, st);
+        }
         return launch_tile<FLUX, MODE, 8, 8>(A, st);
       }
     }

@@ -6,6 +6,8 @@ one application of the operator <= 1e-12 relative L-inf (a few rounding
 errors per term), 100 steps <= 1e-11 relative L-inf.
 """
 import math
+import os
+import subprocess
 import sys
 
 import numpy as np
@@ -310,29 +312,64 @@ def test_tile_shape_independence(kind, p):
         assert torch.equal(U, outs[0][0]) and torch.equal(L, outs[0][1])
 
 
-@pytest.mark.parametrize("kind", ["rot2d", "burgers2d"])
-def test_one_wave_and_four_wave_tiles_at_a_larger_mesh(kind):
-    """232^2 cells: 841 8x8 tiles, more than three per compute unit on 256,
-    so 8x8 runs the one-wave tile kernel there (small meshes take the
-    four-wave tile); 3 steps and one operator on 8x8 and 16x16 tiles, P2
-    WENO on a rough state, bitwise equal."""
-    _note(f"[tiles 232^2] {kind}")
-    w = _mesh(kind, 2, 2, n2=(232, 232))
-    if kind == "rot2d":
-        w.cy = 0.4537
-    g = _dg().DG.from_workload(w)
-    g.set_fused(0)
-    U0 = g.initial_state(w)
-    gen = torch.Generator(device=U0.device).manual_seed(9)
-    U0 = U0 + 0.02 * U0.abs().max() * torch.randn(U0.shape, generator=gen, device=U0.device, dtype=U0.dtype)
-    outs = []
-    for tile in ((8, 8), (16, 16)):
-        g.set_tile(*tile)
-        U = U0.clone()
-        g.run(U, w.dt(), 3)
-        outs.append((U, g.rhs(U0)))
-    torch.cuda.synchronize()
-    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+@pytest.fixture(scope="module")
+def four_wave_limits(tmp_path_factory):
+    """8x8 tiles per compute unit up to which a problem's stages take four waves per tile (0: always one): the library's
+    own rule, by (degree, kernel mode, exterior state)."""
+    d = tmp_path_factory.mktemp("limits")
+    src = d / "limits.hip"
+    src.write_text('#include <cstdio>\n#include "%s"\nint main() {\n  for (int p = 1; p <= 4; ++p)\n'
+                   '    for (int m = 0; m <= 4; ++m)\n      for (int b = 0; b < 2; ++b)\n'
+                   '        std::printf("%%d %%d %%d %%d\\n", p, m, b, dgk::roles_tiles_per_cu(p, m, b));\n}\n'
+                   % os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2309_12019_amd",
+                                  "csrc", "dg_kernels.hpp"))
+    exe = str(d / "limits")
+    subprocess.run(["/opt/rocm/bin/hipcc", "--offload-host-only", "-O0", "-std=c++17", "-fconstexpr-steps=100000000",
+                    str(src), "-o", exe], check=True, capture_output=True)
+    out = subprocess.run([exe], check=True, capture_output=True, text=True).stdout
+    return {tuple(map(int, l.split()[:3])): int(l.split()[3]) for l in out.splitlines()}
+
+
+@pytest.mark.parametrize("kind", ["rot2d", "burgers2d", "riemann"])
+@pytest.mark.parametrize("p", [1, 2, 3, 4])
+@pytest.mark.parametrize("mode", ["dg", "zhao", "weno", "general"])
+def test_one_wave_and_four_wave_tiles(kind, p, mode, four_wave_limits):
+    """8x8 tiles on both sides of the four-wave limit (the first mesh whose tiles exceed it takes one wave per tile, where
+    it is more than 0 the one before takes four) against 16x16 tiles: 3 steps and one operator on a rough state of a
+    ragged mesh, bitwise equal."""
+    if kind == "riemann" and (p > 2 or mode == "dg"):
+        pytest.skip("the exact exterior state: the paper's degrees and sensors")
+    code = {"dg": 0, "zhao": 3, "weno": 2, "general": 2}[mode]
+    limit = four_wave_limits[p, 4 if mode == "weno" else code, int(kind == "riemann")]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    k = math.isqrt(limit * cus)          # k x k tiles are at the limit or below it
+    for m, waves in (((k, 4),) if limit else ()) + ((max(k + 1, 5), 1),):
+        assert (m * m <= limit * cus) == (waves == 4)
+        n = 8 * m - (0 if kind == "riemann" else 3)      # (its quadrants are made of whole cells)
+        _note(f"[8x8 tiles] {kind} P{p} {mode} {n}^2: {m * m} tiles, {waves} wave(s) each")
+        if kind == "riemann":
+            w = inputs.burgers2d_riemann(n, p, mode=code, steps=1)
+        else:
+            w = _mesh(kind, p, code, n2=(n, n))
+            w.cy = 0.4537
+        if mode == "general":
+            w.q, w.r = 2.0, 3.0
+        g = _dg().DG.from_workload(w)
+        g.set_fused(0)
+        U0 = g.initial_state(w)
+        gen = torch.Generator(device=U0.device).manual_seed(9)
+        U0 = U0 + 0.02 * U0.abs().max() * torch.randn(U0.shape, generator=gen, device=U0.device, dtype=U0.dtype)
+        outs = []
+        for tile in ((8, 8), (16, 16)):
+            g.set_tile(*tile)
+            g.set_time(0.0)
+            U = U0.clone()
+            g.run(U, w.dt(), 3)
+            g.set_time(0.0)
+            outs.append((U, g.rhs(U0)))
+        torch.cuda.synchronize()
+        assert torch.isfinite(outs[1][0]).all()
+        assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
 
 
 def test_stable_dt_and_finite_check():
