@@ -319,7 +319,7 @@ int copy_back(dg_ctx* c, hipStream_t st, double* U, const double* from) {
 
 // Whether runs take the 1D kernel of many steps per launch (line_kernel): any
 // order, except where the fused step kernels are switched off.
-bool uses_line(const dg_ctx* c) { return c->d.dim == 1 && c->fused_mode != 0; }
+bool uses_line(const dg_ctx* c) { return c->d.dim == 1 && c->fused_mode != 0 && dgk::line_takes(c->d.nx); }
 
 // nsteps >= 2 steps of a 1D problem on U in place.  A mesh of one workgroup
 // is updated in place; otherwise the launches alternate between U and U1

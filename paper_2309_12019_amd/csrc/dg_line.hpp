@@ -68,6 +68,10 @@ __host__ __device__ inline bool line_cell(const LineArgs& B, int tile, int t, in
   return t < B.own + 2 * B.halo;
 }
 
+// Whether this kernel takes a mesh of nx cells: every index a thread forms
+// (line_cell) stays below 2^31.  (Meshes beyond run their stages one by one.)
+inline bool line_takes(int nx) { return nx <= 2147483647 - 2 * kLineThreads; }
+
 // Launch shape for a mesh of nx cells and a run of nsteps steps (every count of
 // the type).
 // Up to kLineThreads cells: one workgroup, any number of steps.  Beyond:

@@ -87,6 +87,20 @@ int main() {
           bad += line_launch_steps(nsteps, n, n - 1) > p.steps || line_launch_steps(nsteps, n, 0) > p.steps;
           ++launches;
         }
+  // the largest meshes: no index of the last window's threads beyond int
+  for (int nx : {(1 << 30) + 1, 2147483647 - 600, 2147483647 - 512, 2147483647 - 300, 2147483647 - 200, 2147483647 - 150,
+                 2147483647})
+    for (int nv : {2, 15})
+      for (int order : {2, 3, 4}) {
+        if (!line_takes(nx)) continue;
+        const LinePlan p = line_plan(nx, nv, order, 256, 10, nv > 5);
+        const long long grid = ((long long)nx + p.own - 1) / p.own;
+        const bool over = (long long)nx + p.own - 1 > 2147483647ll ||
+                          (grid - 1) * p.own - p.halo + p.threads - 1 > 2147483647ll;
+        if (over) std::printf("nx %d nv %d order %d: an index past int\n", nx, nv, order);
+        bad += over;
+      }
+  for (int nx : {1, 64, 1 << 30, 2147483647 - 600}) bad += !line_takes(nx);
   // (the Euler system at P4 on large meshes takes one step per launch: the
   // odd counts there end in a copy)
   for (int order : {3, 4}) {
