@@ -210,12 +210,14 @@ int dg_step_static(const dg_mesh_desc* desc, double* U, double dt, double t);
 /* nsteps SSP steps of size dt (eq. ssp, or the order rk_order selects), in
  * place on U (device): the fully discrete scheme of Sec. 2 run over a fixed
  * step, the stabilisation of Secs. 3 and 4 re-evaluated in every stage.
- * The stage launches (3, 2 or 6 per step; one fused launch per step where
- * dg_set_fused selects it) are recorded once into a HIP graph (cached for the
+ * The stage launches (rk_order 2 or 3: as many per step, 4: five in 2D and
+ * six in 1D; one fused launch per step where dg_set_fused selects it) are
+ * recorded once into a HIP graph (cached for the
  * same U, dt and chunk length) and replayed on the context stream.  In 1D a
  * run of two or more steps takes many steps per launch instead, without a
- * graph (the steps of a whole mesh of up to 256 cells, a window of cells and
- * its halo beyond; bitwise the same results), unless dg_set_fused is 0.  With
+ * graph (the steps of a whole mesh of up to 256 cells, 128 for the Euler
+ * system, a window of cells and its halo beyond; bitwise the same results),
+ * unless dg_set_fused is 0.  With
  * bc_kind RIEMANN the stages read their times (on which the exterior state
  * depends) as offsets from a device copy of the context clock, which a
  * one-thread launch sets before each replay, so the same graph serves any
@@ -261,7 +263,7 @@ int dg_get_tile(const dg_ctx* ctx, int32_t* tx, int32_t* ty);
  * HBM once.  Same per-cell arithmetic as the per-stage kernel, so results are
  * bitwise the same.  The Euler system has a step kernel of its own (three
  * components per cell, walls handled by the cell code).  Used by dg_step and
- * dg_run.  mode: -1 automatic (default: on in 1D (for the Euler system up
+ * dg_run; in 1D by dg_step and runs of one step only (longer ones: dg_run).  mode: -1 automatic (default: on in 1D (for the Euler system up
  * to four 256-cell tiles per compute unit), and in 2D for meshes of at most
  * one 16x16 tile per compute unit, where per-stage launches are latency
  * bound, and of at most four for degree 1 and for degree-2 Burgers, except
@@ -269,7 +271,7 @@ int dg_get_tile(const dg_ctx* ctx, int32_t* tx, int32_t* ty);
  * DG_EINVAL for another mode, DG_EUNSUPPORTED for mode 1 when the three
  * tiles exceed LDS (2D degree 4), rk_order is not 3 or bc_kind is not
  * CONSTANT; in those cases the automatic mode never uses it.  dg_get_fused
- * writes 1 if steps use it.
+ * writes 1 if steps use it (in 1D: single steps).
  * Mode 0 also makes dg_run of a 1D problem launch its stages one by one, and
  * the adjoint (below) launch its two passes of every stage
  * separately instead of sharing launches between consecutive stages; the

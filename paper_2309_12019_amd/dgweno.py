@@ -310,8 +310,9 @@ class DG:
         _check(self.lib.dg_set_tile(self.h, int(tx), int(ty)))
 
     def set_fused(self, mode: int) -> None:
-        """Fused step kernel: -1 automatic, 0 off, 1 on (dg_set_fused); 0 also
-        gives the adjoint separate launches for its two passes."""
+        """Fused step kernel: -1 automatic, 0 off, 1 on (dg_set_fused; in 1D
+        that of single steps); 0 also gives the adjoint separate launches for
+        its two passes and 1D runs one launch per stage."""
         _check(self.lib.dg_set_fused(self.h, int(mode)))
 
     def fused(self) -> bool:

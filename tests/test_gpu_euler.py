@@ -101,7 +101,7 @@ def test_sod_100_steps(p, mode):
     U0 = O.project(w.ic)
     ref = O.run(U0, w.dt(), 100)
     g = _dg().DG.from_workload(w)
-    assert g.fused()                          # small 1D meshes: the fused step kernel by default
+    assert g.fused()                          # small 1D meshes: single steps on the fused kernel by default
     outs = []
     for fused in (1, 0):
         g.set_fused(fused)
@@ -109,7 +109,7 @@ def test_sod_100_steps(p, mode):
         g.run(U, w.dt(), 100)
         torch.cuda.synchronize()
         err = relinf(U.cpu().reshape(ref.shape), ref)
-        _note(f"    {'fused' if fused else 'per-stage'}: rel Linf = {err:.3e}")
+        _note(f"    {'many steps per launch' if fused else 'per-stage'}: rel Linf = {err:.3e}")
         assert err <= 1e-11
         outs.append(U)
     assert torch.equal(outs[0], outs[1])
@@ -218,8 +218,8 @@ def test_degenerate_and_ragged_meshes(n, periodic):
 
 
 def test_run_equals_repeated_step_bitwise():
-    """Graph replay (dg_run: one 64-step graph and a 6-step graph) against 70
-    eager steps, Sod 128 P2 WENO."""
+    """A run (70 steps in one launch) against 70 single steps (the fused step
+    kernel), Sod 128 P2 WENO."""
     _note("[euler determinism] dg_run vs dg_step")
     w = _workload(128, 2, inputs.MODE_WENO)
     g = _dg().DG.from_workload(w)
@@ -256,9 +256,9 @@ def test_tile_shape_independence(p):
                                                 (600, True, 4, inputs.MODE_ZHAO), (600, False, 2, inputs.MODE_DG)])
 def test_fused_step_equals_stage_launches(n, periodic, p, mode):
     """The fused Euler step (three stages in one launch on a tile with three
-    rings) against three stage launches: bitwise equal after 30 steps, with
-    walls and periodic meshes, ragged tiles, a single cell, every degree and
-    mode."""
+    rings; taken by single steps) and a run (many steps per launch) against
+    three stage launches: bitwise equal after 12 steps and 30 more, with walls
+    and periodic meshes, ragged tiles, a single cell, every degree and mode."""
     _note(f"[euler fused] n={n} periodic={periodic} P{p} mode={mode}")
     w = _workload(n, p, mode, periodic)
     if n < 8:
@@ -269,10 +269,14 @@ def test_fused_step_equals_stage_launches(n, periodic, p, mode):
         g.set_fused(fused)
         assert g.fused() == bool(fused)
         U = g.initial_state(w)
+        for _ in range(12):
+            g.step(U, w.dt())
+        V = U.clone()
         g.run(U, w.dt(), 30)
         torch.cuda.synchronize()
-        outs.append(U)
-    assert torch.equal(outs[0], outs[1])
+        outs.append((V, U))
+    assert torch.equal(outs[0][0], outs[1][0])
+    assert torch.equal(outs[0][1], outs[1][1])
 
 
 def test_full_size_parity():
@@ -285,7 +289,7 @@ def test_full_size_parity():
     O = _oracle(w)
     U0 = O.project(w.ic)
     g = _dg().DG.from_workload(w)
-    assert g.tile() == (256, 1) and not g.fused()   # 4096 tiles: the per-stage kernel
+    assert g.tile() == (256, 1) and not g.fused()   # 4096 tiles: the per-stage kernel (runs: many steps per launch)
     Ug = g.initial_state(w)
     torch.cuda.synchronize()
     assert relinf(Ug.cpu().reshape(U0.shape), U0) <= 1e-13
