@@ -1430,8 +1430,10 @@ __device__ inline void stage_tile(const StageArgs& A, double* lds, int ix0, int 
 }
 
 // Waves per SIMD the stage kernels are held to: two at P4, where their
-// registers are within a few of the limit for it (231-262 of 256 VGPRs, up
-// to 15 spilled).
+// registers are within a few of the limit for it (244-256 VGPRs; up to 2
+// spilled in single problems, 15 and, on persistent 8x8 grids, 27 in batches.
+// The KPP flux on 16x16 tiles spills 268 and is faster all the same: 300^2 329
+// -> 309 us per step).
 __host__ __device__ constexpr int stage_min_waves(int dim, int p, int mode) {
   return dim == 2 && p == 4 && mode == MODE_WENO1 ? 2 : 1;
 }

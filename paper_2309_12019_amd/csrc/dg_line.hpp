@@ -21,9 +21,9 @@
 // large one is bound by its arithmetic, where the threads of a launch per
 // step idle at the tile's ends (five waves for 262 of 320 cells) and the
 // per-stage Euler kernel moves the state seven times a step.  Per step, one
-// launch per step or stage -> this kernel: 64 cells P2 advection 4.4 -> 2.0
-// us, 1024 cells P3 fourth order 17.4 -> 4.3, Sod 128 cells P2 8.0 -> 5.5,
-// Sod 2^20 cells P2 121 -> 79.
+// launch per step or stage -> this kernel: 64 cells P2 advection 4.4 -> 1.5
+// us, 1024 cells P3 fourth order 17.4 -> 3.5, Sod 128 cells P2 8.0 -> 3.7,
+// Sod 2^20 cells P2 121 -> 67.
 #pragma once
 
 #include "dg_euler.hpp"
@@ -81,15 +81,20 @@ inline bool line_takes(int nx) { return nx <= 2147483647 - 2 * kLineThreads; }
 // While every window has a compute unit of its own the halo costs nothing, so
 // the longest launch wins (halo <= 48 of 256 threads); past that the sum of
 // the two costs is minimised, with kLineEval us of a compute unit's time per
-// operator evaluation of a window and stored value of a cell.
+// operator evaluation of a window and stored value of a cell.  (Fixed costs of
+// 3 to 6 and 0.10 instead of 0.14 stay within 1 % of it in the mean of 432
+// runs, advection, Burgers and Sod at 30000 to 2^20 cells, every degree and
+// order, and lose up to 50 % in single ones.)
 constexpr int kLineMaxHalo = 48;
 constexpr int kLineChunk = 128;  // steps per launch of a mesh of one workgroup
 constexpr double kLineFixed = 4.0, kLineEval = 0.14;
 //   The Euler system takes split windows while each has a compute unit of its
 // own (128 cells, halo <= 24).  Sod P2, per step, whole cells -> split: 128
-// cells 4.26 -> 3.85 us, 1000 cells 4.71 -> 4.20, 15000 cells 4.76 -> 4.29
-// (P1 3.44 -> 2.99 at 128, P4 6.43 -> 5.98); past that, windows share compute
-// units and whole cells are cheaper.
+// cells 4.39 -> 3.75 us, 256 cells (one workgroup -> windows relaunched every
+// eight steps) 4.61 -> 4.16, 1000 cells 4.87 -> 4.21, 15000 cells 4.91 -> 4.25
+// (P1 3.42 -> 2.90 at 128, P4 6.51 -> 5.91); past that, windows share compute
+// units and whole cells are cheaper.  Without a sensor the split gains less,
+// and at P1 and P4 it loses up to 10 % between 129 and 256 cells.
 constexpr int kLineSplitMaxHalo = 24;
 struct LinePlan {
   int threads, own, halo, steps;
