@@ -187,8 +187,13 @@ __host__ __device__ constexpr int line_lds_doubles(int nv, bool split) {
 // 2.5 ns however independent it is of its neighbours, so an evaluation takes
 // what its longest wave has, instead of what a cell has (641 instructions at
 // P2), and one more barrier.
+// The Euler system's whole cells at P4 are held to two waves per SIMD: left to
+// itself the compiler takes 1 to 8 registers more than that with the sensor of
+// the paper's exponents, and a compute unit then holds one workgroup (Sod P4
+// per step, one -> two: 65536 cells 17.3 -> 14.6 us, 2^20 cells 192 -> 125).
 template <int P, int FLUX, int MODE, int RK, bool SPLIT = false>
-__global__ void __launch_bounds__(SPLIT ? kLineSplitThreads : kLineThreads) line_kernel(const LineArgs B) {
+__global__ void __launch_bounds__(SPLIT ? kLineSplitThreads : kLineThreads,
+                                  FLUX == FLUX_EULER && P == 4 && !SPLIT ? 2 : 1) line_kernel(const LineArgs B) {
   static_assert(!SPLIT || FLUX == FLUX_EULER, "the scalar fluxes' cells are too short to split");
   using LC = LineCell<P, FLUX, MODE, SPLIT ? kLineSplitCells : kLineThreads>;
   constexpr int NV = LC::NV, S = LC::S;
