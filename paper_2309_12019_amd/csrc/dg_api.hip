@@ -345,7 +345,8 @@ int line_steps(dg_ctx* c, hipStream_t st, double* U, double dt, int nsteps) {
     d[5] = dt * kB54 / kA54;
   }
   const bool euler = c->d.flux == DG_FLUX_EULER;
-  const LinePlan p = line_plan(c->d.nx, c->nl, r.order, c->cus, nsteps, euler);
+  const LinePlan p = line_plan(c->d.nx, c->nl, r.order, c->cus, nsteps, euler,
+                               c->d.mode == DG_MODE_WENO || c->d.mode == DG_MODE_ZHAO);
   const bool one = p.halo == 0;  // the whole mesh in one workgroup
   r.threads = p.threads;
   r.line.own = p.own;

@@ -93,17 +93,19 @@ constexpr double kLineFixed = 4.0, kLineEval = 0.14;
 // cells 4.39 -> 3.75 us, 256 cells (one workgroup -> windows relaunched every
 // eight steps) 4.61 -> 4.16, 1000 cells 4.87 -> 4.21, 15000 cells 4.91 -> 4.25
 // (P1 3.42 -> 2.90 at 128, P4 6.51 -> 5.91); past that, windows share compute
-// units and whole cells are cheaper.  Without a sensor the split gains less,
-// and at P1 and P4 it loses up to 10 % between 129 and 256 cells.
+// units and whole cells are cheaper.  Over 64 to 19000 cells, every degree,
+// order and mode, the split takes .84 to .99 of the whole cells' time (1.05 at
+// most, Zhao between 129 and 256 cells), but 1.02 to 1.11 with the fourth order
+// at P4 without a sensor, where it spills: that one takes whole cells.
 constexpr int kLineSplitMaxHalo = 24;
 struct LinePlan {
   int threads, own, halo, steps;
   bool split;
 };
-inline LinePlan line_plan(int nx, int nv, int order, int cus, int nsteps, bool euler) {
+inline LinePlan line_plan(int nx, int nv, int order, int cus, int nsteps, bool euler, bool sensor) {
   const int ev = rk_evals(order);
   const int steps = nsteps / 2 + nsteps % 2;  // windows alternate between two arrays: two launches at least
-  if (euler) {
+  if (euler && (sensor || nv < 15 || order < 4)) {
     if (nx <= kLineSplitCells) return {kLineSplitThreads, nx, 0, kLineChunk, true};
     const int s = steps < kLineSplitMaxHalo / ev ? steps : kLineSplitMaxHalo / ev;
     const int own = kLineSplitCells - 2 * ev * s;

@@ -16,9 +16,10 @@ int main() {
     for (int order : {2, 3, 4})
       for (int nv : {2, 5, 6, 15})
         for (int nsteps : {2, 3, 4, 9, 10, 128})
-          for (int per : {0, 1}) {
-            const bool euler = nv > 5;
-            const LinePlan p = line_plan(nx, nv, order, 256, nsteps, euler);
+          for (int pers : {0, 1, 2, 3}) {
+            const int per = pers & 1;
+            const bool euler = nv > 5, sensor = pers < 2;
+            const LinePlan p = line_plan(nx, nv, order, 256, nsteps, euler, sensor);
             // cells a workgroup holds, its threads, its LDS slots
             const int cells = p.split ? kLineSplitCells : kLineThreads;
             const int slots = p.split ? TileGeom<1, kLineSplitCells, 1>::S : TileGeom<1, kLineThreads, 1>::S;
@@ -66,7 +67,7 @@ int main() {
       for (int nv : {2, 5, 6, 15})
         for (int nsteps : {2, 3, 5, 15, 16, 17, 127, 128, 129, 1000, 65537, 1 << 30, 2147483519, 2147483520, 2147483600,
                            2147483646, 2147483647}) {
-          const LinePlan p = line_plan(nx, nv, order, 256, nsteps, nv > 5);
+          const LinePlan p = line_plan(nx, nv, order, 256, nsteps, nv > 5, nsteps % 2);
           const long long n = line_launches(p, nsteps);
           const bool bounds = p.own >= 1 && p.steps >= 1 && n >= 1 && (p.halo == 0 || n % 2 == 0 || n == nsteps) &&
                               (p.halo == 0 || p.halo == rk_evals(order) * p.steps);
@@ -93,7 +94,7 @@ int main() {
     for (int nv : {2, 15})
       for (int order : {2, 3, 4}) {
         if (!line_takes(nx)) continue;
-        const LinePlan p = line_plan(nx, nv, order, 256, 10, nv > 5);
+        const LinePlan p = line_plan(nx, nv, order, 256, 10, nv > 5, true);
         const long long grid = ((long long)nx + p.own - 1) / p.own;
         const bool over = (long long)nx + p.own - 1 > 2147483647ll ||
                           (grid - 1) * p.own - p.halo + p.threads - 1 > 2147483647ll;
@@ -104,7 +105,7 @@ int main() {
   // (the Euler system at P4 on large meshes takes one step per launch: the
   // odd counts there end in a copy)
   for (int order : {3, 4}) {
-    const LinePlan p = line_plan(900001, 15, order, 256, 3, true);
+    const LinePlan p = line_plan(900001, 15, order, 256, 3, true, true);
     bad += p.steps != 1 || line_launches(p, 3) != 3;
   }
   std::printf("%d launches, %d failures\n", launches, bad);

@@ -70,3 +70,19 @@ def test_odd_runs_of_one_step_per_launch(order, kind):
     torch.cuda.synchronize()
     assert torch.isfinite(out[1]).all() and not torch.equal(out[1], U0)
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("n", [1, 128, 129, 256, 257, 1000])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_fourth_order_p4_without_a_sensor(n, mode):
+    """The one Euler kernel that takes whole cells at every size."""
+    from paper_2309_12019_amd import dgweno
+    w = _problem("sod", n, 4, 4, mode)
+    g = dgweno.DG.from_workload(w)
+    U0 = g.initial_state(w)
+    out = []
+    for fused in (-1, 0):
+        g.set_fused(fused)
+        out.append(g.run(U0.clone(), w.dt() / 4, 11))
+    torch.cuda.synchronize()
+    assert torch.isfinite(out[1]).all() and torch.equal(out[0], out[1])
