@@ -131,6 +131,7 @@ int class_stage(dg_batch* b, Class& c, hipStream_t st, const double* uin, const 
   r.args.ty = c.ty;
   r.ncells = class_grid(b, c);
   r.batch_one = c.grid_per_cu == 0;
+  r.batch_large = dgk::batch_fewer_rounds((long long)c.ntiles * c.tx * c.ty, b->cus);
   r.stream = st;
   r.batch.probs = b->d_probs;
   r.batch.tiles = c.d_tiles;

@@ -1277,14 +1277,28 @@ __device__ inline void store_second(const StageArgs& A, size_t cell, const doubl
 //     settled: 512^2 rotation 114 -> 106 / 148 -> 126, Burgers 130 -> 121 /
 //     163 -> 143; see kUnsettledCells), P3 on single meshes (Zhao 400^2 71.3 ->
 //     60.2), and the KPP flux in batches (24 x 64^2 LO P3 226 -> 146, P4 323 ->
-//     194).  Not batches at P3 (LO, 4 x 48^2 22.8 -> 24.2, 24 x 64^2 37.8 ->
-//     41.4), P1 and P2 (1 to 4 %) and 1D (batch of 4 x 960 cells, LO P2 10.6
+//     194).  Not small batches at P3 (LO, 4 x 48^2 22.8 -> 24.2, 24 x 64^2 37.8
+//     -> 41.4; see batch_fewer_rounds), P1 and P2 (1 to 4 %) and 1D (batch of 4 x 960 cells, LO P2 10.6
 //     -> 11.2).
 template <int DIM, int P, int FLUX, int MODE>
 __host__ __device__ constexpr bool stage_settles(bool batch) {
   if (MODE == MODE_WENO1) return true;
   if (MODE == MODE_WENO || DIM == 1) return false;
   return FLUX == FLUX_KPP ? batch : P == 4 || (P == 3 && !batch);
+}
+
+// P3 batches of those modes, one workgroup per tile, settle where that saves a
+// round: settled, a compute unit holds three of their 16x16 tiles (three waves
+// per SIMD), else two.  Settled over unsettled by 16x16 tiles per compute unit
+// (DG, LO and Zhao, rotation and Burgers): 1.00 to 1.10 up to 2, .87 to .92 at
+// 3, .99 to 1.04 at 4, .92 to .99 at 6 and 8, .90 to .98 at 11 and 12.
+inline bool batch_fewer_rounds(long long cells, int cus) {
+  const long long all = 256ll * cus;
+  return (cells + 3 * all - 1) / (3 * all) < (cells + 2 * all - 1) / (2 * all);
+}
+template <int DIM, int P, int FLUX, int MODE>
+__host__ __device__ constexpr bool large_batch_settles() {
+  return DIM == 2 && P == 3 && FLUX != FLUX_KPP && !is_weno(MODE);
 }
 
 // P4 of the modes without a sensor beyond this many cells (three states of
@@ -2089,7 +2103,7 @@ __device__ inline T load_uniform(const T* p) {
   return t;
 }
 
-template <int DIM, int P, int FLUX, int MODE, int TX, int TY>
+template <int DIM, int P, int FLUX, int MODE, int TX, int TY, bool SETTLE>
 __device__ inline void batch_tile(const BatchStageArgs& B, double* lds, int k) {
   const BatchTile tl = load_uniform(B.tiles + k);
   BatchProblem pr;
@@ -2107,22 +2121,22 @@ __device__ inline void batch_tile(const BatchStageArgs& B, double* lds, int k) {
   A.a = B.a;
   A.b = B.b;
   A.rhs_only = 0;
-  stage_tile<DIM, P, FLUX, MODE, TX, TY, false, false, stage_settles<DIM, P, FLUX, MODE>(true)>(A, lds, tl.ix0,
-                                                                                              tl.iy0);
+  stage_tile<DIM, P, FLUX, MODE, TX, TY, false, false, SETTLE>(A, lds, tl.ix0, tl.iy0);
 }
 
 // ONE: one workgroup per tile (grid = the number of tiles), no tile loop;
 // a loop makes the compiler keep the arithmetic's loop-invariant values in
 // registers across tiles (tens of VGPRs more), which this form avoids.
-template <int DIM, int P, int FLUX, int MODE, int TX, int TY, bool ONE = false>
+template <int DIM, int P, int FLUX, int MODE, int TX, int TY, bool ONE = false,
+          bool SETTLE = stage_settles<DIM, P, FLUX, MODE>(true)>
 __global__ void __launch_bounds__(DIM == 2 ? TX * TY : TX, stage_min_waves(DIM, P, MODE))
     batch_stage_kernel(const BatchStageArgs B) {
   extern __shared__ double lds[];
   if constexpr (ONE) {
-    if ((int)blockIdx.x < B.ntiles) batch_tile<DIM, P, FLUX, MODE, TX, TY>(B, lds, blockIdx.x);
+    if ((int)blockIdx.x < B.ntiles) batch_tile<DIM, P, FLUX, MODE, TX, TY, SETTLE>(B, lds, blockIdx.x);
   } else {
     for (int k = blockIdx.x; k < B.ntiles; k += gridDim.x) {
-      batch_tile<DIM, P, FLUX, MODE, TX, TY>(B, lds, k);
+      batch_tile<DIM, P, FLUX, MODE, TX, TY, SETTLE>(B, lds, k);
       tile_barrier();  // the next tile reuses LDS
     }
   }

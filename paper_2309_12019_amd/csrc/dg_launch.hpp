@@ -33,6 +33,7 @@ struct LaunchReq {
   hipStream_t stream;
   BatchStageArgs batch;  // LAUNCH_BATCH (tile shape in args.tx/args.ty, grid in ncells)
   int batch_one;         // LAUNCH_BATCH: one workgroup per tile (grid = batch.ntiles)
+  int batch_large;       // LAUNCH_BATCH: settled tiles take fewer rounds (batch_fewer_rounds)
   AdjArgs adj;           // LAUNCH_ADJ_* (tile shape in adj.s.tx/adj.s.ty)
   LineArgs line;         // LAUNCH_LINE (1D; line.s, not args)
   int order, threads;    // LAUNCH_LINE: Runge-Kutta order, threads per workgroup

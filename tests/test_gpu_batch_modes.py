@@ -69,3 +69,13 @@ def test_kpp_p4_batches_take_16x16_tiles_past_four_small_ones_per_compute_unit(n
     B = _check([w], steps=1)
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
         assert (B.schedule(0)["tx"], B.schedule(0)["ty"]) == (tile, tile)
+
+
+@pytest.mark.parametrize("mode", [0, 1, 3])
+@pytest.mark.parametrize("kind", ["rot2d", "burgers2d"])
+def test_p3_batches_on_both_sides_of_the_large_kernel(kind, mode):
+    """512 tiles of 16x16 cells (on 256 compute units two each: as many rounds either way) and one row of tiles more (fewer
+    rounds settled)."""
+    make = inputs.rot2d if kind == "rot2d" else inputs.burgers2d
+    for ny in (128, 129):
+        _check([make(512, 3, seed=1, ny=128, mode=mode, steps=1), make(512, 3, seed=2, ny=ny, mode=mode, steps=1)], steps=1)
