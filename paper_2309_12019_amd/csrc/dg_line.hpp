@@ -94,9 +94,10 @@ constexpr double kLineFixed = 4.0, kLineEval = 0.14;
 // eight steps) 4.61 -> 4.16, 1000 cells 4.87 -> 4.21, 15000 cells 4.91 -> 4.25
 // (P1 3.42 -> 2.90 at 128, P4 6.51 -> 5.91); past that, windows share compute
 // units and whole cells are cheaper.  Over 64 to 19000 cells, every degree,
-// order and mode, the split takes .84 to .99 of the whole cells' time (1.05 at
-// most, Zhao between 129 and 256 cells), but 1.02 to 1.11 with the fourth order
-// at P4 without a sensor, where it spills: that one takes whole cells.
+// order and mode, the split takes .84 to 1.02 of the whole cells' time (up to
+// 1.05 between 129 and 256 cells, where windows stand against one workgroup), but
+// 1.02 to 1.11 with the fourth order at P4 without a sensor, where it spills:
+// that one takes whole cells.
 constexpr int kLineSplitMaxHalo = 24;
 struct LinePlan {
   int threads, own, halo, steps;
